@@ -236,7 +236,9 @@ typedef enum {
  * other kernels, and reported as 0 for them).  For CPI_REFOCUS_VIEW_ROWS,
  * rows_per_wave holds the output columns per work-group instead, with
  * (planes, columns) in (8, 8), (4, 16), (8, 16), (16, 16), (8, 32), and
- * view_splits is ignored. */
+ * view_splits is ignored; plane sets whose view windows fit in registers are
+ * split by the library itself, whichever of these is named (the sums and
+ * their order are the same). */
 typedef struct {
   int32_t planes_per_group;
   int32_t rows_per_wave;

@@ -26,6 +26,7 @@ SOURCES = [
     "kernels_f32.hip",
     "kernels_refocus.hip",
     "kernels_refocus_rows.hip",
+    "kernels_refocus_window.hip",
     "autotune.hip",
     "peaks.hip",
     "kernels_nn.hip",

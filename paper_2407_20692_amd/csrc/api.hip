@@ -303,19 +303,27 @@ cpi_status refocus_enqueue(const float* gamma, const cpi_geometry* g, const doub
   }
   RefocusConfig c = forced ? *forced : refocus_config_for(g, n_alpha);
   float* partial = reinterpret_cast<float*>(ws + pl.off_partial);
-  if (c.mode == 2 && !forced && !rows_supported(rg, alphas, n_alpha, c.kp, c.rw, pl.rows_chunk)) {
-    // the configured row-lane shape does not take this plane set: the next
-    // shape whose windows hold it, in order of pairs per work-group
-    for (const auto& t : {std::make_pair(8, 32), std::make_pair(16, 16), std::make_pair(8, 16),
-                          std::make_pair(16, 8), std::make_pair(8, 8), std::make_pair(4, 16)})
-      if (rows_supported(rg, alphas, n_alpha, t.first, t.second, pl.rows_chunk)) {
-        c.kp = t.first;
-        c.rw = t.second;
-        break;
-      }
-  }
   if (c.mode == 2) {
-    if (rows_supported(rg, alphas, n_alpha, c.kp, c.rw, pl.rows_chunk)) {
+    // The register-window x pass makes its own split of the work and takes
+    // every plane set whose windows fit it; an explicit configuration also
+    // has to be one that the LDS-tap x pass would take.
+    WindowSplit sp;
+    const bool window = window_split(rg, alphas, n_alpha, pl.rows_chunk, &sp);
+    bool taps = (!window || forced) &&
+                rows_supported(rg, alphas, n_alpha, c.kp, c.rw, pl.rows_chunk);
+    if (!window && !taps && !forced) {
+      // the next LDS-tap shape whose windows hold the plane set, in order of
+      // pairs per work-group
+      for (const auto& t : {std::make_pair(8, 32), std::make_pair(16, 16), std::make_pair(8, 16),
+                            std::make_pair(16, 8), std::make_pair(8, 8), std::make_pair(4, 16)})
+        if (rows_supported(rg, alphas, n_alpha, t.first, t.second, pl.rows_chunk)) {
+          c.kp = t.first;
+          c.rw = t.second;
+          taps = true;
+          break;
+        }
+    }
+    if (taps || (window && !forced)) {
       RowsWorkspace w;
       w.xe = reinterpret_cast<int32_t*>(ws + pl.off_rows_xe);
       w.yr = reinterpret_cast<int2*>(ws + pl.off_rows_yr);
@@ -323,8 +331,10 @@ cpi_status refocus_enqueue(const float* gamma, const cpi_geometry* g, const doub
       w.chunk = int(pl.rows_chunk);
       w.wout_cap = pl.rows_wout_cap;
       ProfScope ps("refocus_batched", st);
-      CPI_HIP(refocus_rows(gamma, rg, alphas, itab, ftab, ws + pl.off_ytab, pl.table_stride,
-                           n_alpha, c.kp, c.rw, w, out, st),
+      CPI_HIP(window ? refocus_window(gamma, rg, alphas, sp, itab, ftab, ws + pl.off_ytab,
+                                      pl.table_stride, n_alpha, w, out, st)
+                     : refocus_rows(gamma, rg, alphas, itab, ftab, ws + pl.off_ytab,
+                                    pl.table_stride, n_alpha, c.kp, c.rw, w, out, st),
               "refocus");
       return CPI_OK;
     }

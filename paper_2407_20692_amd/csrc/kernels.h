@@ -201,6 +201,26 @@ hipError_t refocus_rows(const float* gamma, const RefGeom& g, const double* alph
                         int n_alpha, int na, int xr, const RowsWorkspace& w, float* out,
                         hipStream_t s);
 
+// Register-window x pass of the row-lane refocus: work split chosen for a
+// geometry and plane set (host), and the pass over one chunk of planes
+// (column tables, then T; row ranges yr as for groups of na planes).
+struct WindowSplit {
+  int np = 0, xc = 0, pg = 0;   // planes x columns per wave, plane groups per work-group
+  int na = 0, xr = 0;           // planes x columns per work-group
+  int blocks = 0;               // 16-column blocks its windows take
+};
+bool window_split(const RefGeom& g, const double* alphas, int n_alpha, int64_t chunk,
+                  WindowSplit* out);
+hipError_t window_xpass(const float* gamma, const RefGeom& g, const double* alphas,
+                        const WindowSplit& w, const int32_t* itab, const float* ftab,
+                        int64_t stride, int first, int count, int32_t* xe, const int2* yr,
+                        float* t, int wout_pad, hipStream_t s);
+// The whole row-lane refocus with that x pass.
+hipError_t refocus_window(const float* gamma, const RefGeom& g, const double* alphas,
+                          const WindowSplit& sp, const int32_t* itab, const float* ftab, const void* ytab,
+                          int64_t stride, int n_alpha, const RowsWorkspace& w, float* out,
+                          hipStream_t s);
+
 // Gamma views resampled on a lens-plane sample grid (x_b, y_b) = (ox + i sx,
 // oy + j sy), i < nx, j < ny: out[j * nx + i][.] = bilinear interpolant of the
 // pb = wb * hb views of pa values at that point (zero outside detector B).

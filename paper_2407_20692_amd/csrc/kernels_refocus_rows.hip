@@ -28,6 +28,10 @@
 // keeps those stores free of bank conflicts.  Work-groups are mapped so that
 // all those of one y_b run on one XCD and share its L2.
 //
+// Plane sets whose windows fit it take the register-window x pass instead
+// (kernels_refocus_window.hip, the same sums in the same order); this one
+// remains for wider windows.
+//
 // Fold pass (k_ref_rows_fold): one thread per output pixel of a plane sums
 // the two T rows of each y_b with the row weights.
 //
@@ -614,6 +618,24 @@ int rows_window_width(const RefGeom& g, const double* alphas, int n_alpha, int n
   return 0;
 }
 
+hipError_t launch_yrange(const GeomI& gi, const YEntry* ytab, const RowsWorkspace& w, int na,
+                         int first, int count, hipStream_t s) {
+  const int64_t groups = (count + na - 1) / na;
+  hipLaunchKernelGGL(k_rows_yrange, dim3(unsigned(groups * gi.hb)), dim3(256), 0, s, gi, ytab,
+                     first, count, na, w.yr);
+  return hipGetLastError();
+}
+
+hipError_t launch_fold(const GeomI& gi, const YEntry* ytab, const RowsWorkspace& w,
+                       int wout_pad, int first, int count, float* out, hipStream_t s) {
+  const int64_t nf = int64_t(gi.out_w) * gi.out_h * count;
+  int64_t gf = (nf + 255) / 256;
+  if (gf > 65536) gf = 65536;
+  hipLaunchKernelGGL(k_ref_rows_fold, dim3(unsigned(gf)), dim3(256), 0, s, gi, ytab, w.t,
+                     wout_pad, first, count, out);
+  return hipGetLastError();
+}
+
 template <int NA, int XR, int WW>
 hipError_t launch_rows_ww(const float* gamma, const GeomI& gi, const int32_t* itab,
                           const float* ftab, const YEntry* ytab, int64_t stride, int n_alpha,
@@ -630,9 +652,7 @@ hipError_t launch_rows_ww(const float* gamma, const GeomI& gi, const int32_t* it
                        ftab, stride, first, count, tiles, WW, w.xe);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_rows_yrange, dim3(unsigned(int64_t(groups) * gi.hb)), dim3(256), 0, s,
-                       gi, ytab, first, count, NA, w.yr);
-    e = hipGetLastError();
+    e = launch_yrange(gi, ytab, w, NA, first, count, s);
     if (e != hipSuccess) return e;
     const int64_t nwg = int64_t(8) * ((gi.hb + 7) / 8) * bands * tiles * groups;
     if (nwg > 0x7fffffff) return hipErrorInvalidValue;
@@ -641,12 +661,7 @@ hipError_t launch_rows_ww(const float* gamma, const GeomI& gi, const int32_t* it
                        gi, w.xe, w.yr, groups, tiles, bands, count, w.t, wout_pad);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int64_t nf = int64_t(gi.out_w) * gi.out_h * count;
-    int64_t gf = (nf + 255) / 256;
-    if (gf > 65536) gf = 65536;
-    hipLaunchKernelGGL(k_ref_rows_fold, dim3(unsigned(gf)), dim3(256), 0, s, gi, ytab, w.t,
-                       wout_pad, first, count, out);
-    e = hipGetLastError();
+    e = launch_fold(gi, ytab, w, wout_pad, first, count, out, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -670,6 +685,28 @@ bool rows_supported(const RefGeom& g, const double* alphas, int n_alpha, int na,
   if (!rows_config_built(na, xr) || chunk < 16 || chunk % 16 != 0 || g.wa < 2 || g.ha < 2)
     return false;
   return rows_window_width(g, alphas, n_alpha, na, xr) != 0;
+}
+
+hipError_t refocus_window(const float* gamma, const RefGeom& g, const double* alphas,
+                          const WindowSplit& sp, const int32_t* itab, const float* ftab, const void* ytab,
+                          int64_t stride, int n_alpha, const RowsWorkspace& w, float* out,
+                          hipStream_t s) {
+  const GeomI gi{g.wa, g.ha, g.wb, g.hb, g.out_w, g.out_h};
+  const YEntry* yt = static_cast<const YEntry*>(ytab);
+  const int wout_pad = (g.out_w + sp.xr - 1) / sp.xr * sp.xr;
+  if (int64_t(wout_pad) > w.wout_cap || w.chunk < 16 || w.chunk % sp.na != 0)
+    return hipErrorInvalidValue;
+  for (int first = 0; first < n_alpha; first += w.chunk) {
+    const int count = n_alpha - first < w.chunk ? n_alpha - first : w.chunk;
+    hipError_t e = launch_yrange(gi, yt, w, sp.na, first, count, s);
+    if (e != hipSuccess) return e;
+    e = window_xpass(gamma, g, alphas, sp, itab, ftab, stride, first, count, w.xe, w.yr, w.t,
+                     wout_pad, s);
+    if (e != hipSuccess) return e;
+    e = launch_fold(gi, yt, w, wout_pad, first, count, out, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t refocus_rows(const float* gamma, const RefGeom& g, const double* alphas,
