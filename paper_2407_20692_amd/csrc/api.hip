@@ -191,17 +191,16 @@ cpi_status enqueue_correlate(const cpi::CorrPlan& pl, const uint8_t* fa, const u
     return CPI_OK;
   }
 
-  // Byte frames: one pass builds bit rows, popcounts and the OR of all bytes.
-  // Binary data (OR <= 1) is then complete; otherwise the device also runs
-  // the byte-sum and int8-row passes and the byte contraction, and skips the
+  // Byte frames: one pass builds bit rows and popcounts, up to the first byte
+  // above 1.  Binary data is then complete; otherwise the device also runs the
+  // byte-row pass (with the byte sums) and the byte contraction, and skips the
   // bit contraction.  Both branches are enqueued; no host synchronisation.
   {
     ProfScope ps("ingest", st);
     const cpi::IngestJob ja{fa, pl.pa, pl.pa_pad, op_a, sum_a, sum2_a, 0};
     const cpi::IngestJob jb{fb, pl.pb, pl.pb_pad, op_b, sum_b, sum2_b, fp4 ? 1 : 0};
     CPI_HIP(cpi::u8_to_bits(ja, jb, pl.n, pl.kpad_bits, stats, st), "ingest");
-    CPI_HIP(cpi::u8_sums(ja, jb, pl.n, stats, st), "sums");
-    CPI_HIP(cpi::u8_to_bytes(ja, jb, pl.n, pl.kpad_bytes, stats, st), "ingest");
+    CPI_HIP(cpi::u8_to_bytes(ja, jb, pl.n, pl.kpad_bytes, pl.row_bytes_bytes, stats, st), "ingest");
   }
 
   ProfScope ps("gemm", st);
@@ -226,6 +225,7 @@ cpi_status enqueue_correlate(const cpi::CorrPlan& pl, const uint8_t* fa, const u
     if (k1 > pl.kpad_bytes) k1 = pl.kpad_bytes;
     gy.k_byte_off = k0;
     gy.kblocks = (k1 - k0) / cpi::kByteBlock;
+    gy.pad_frames = k1 > pl.n ? k1 - pl.n : 0;
     if (pl.passes == 1)
       gy.mode = cpi::EPI_FINAL;
     else if (pass == 0)
@@ -538,11 +538,13 @@ cpi_status cpi_correlate_workspace_size(int64_t n, int64_t pa, int64_t pb, cpi_f
                                         size_t* bytes) {
   return guarded([&]() -> cpi_status {
     if (!bytes) return set_error(CPI_ERR_INVALID_ARG, "bytes is null");
-    cpi::CorrPlan pl;
+    cpi::CorrPlan pl, tight;
     std::string why;
-    cpi_status s = cpi::plan_correlate(n, pa, pb, int(fmt), &pl, &why);
+    cpi_status s = cpi::plan_correlate(n, pa, pb, int(fmt), &pl, &why, cpi::kByteRowLine);
+    if (s == CPI_OK) s = cpi::plan_correlate(n, pa, pb, int(fmt), &tight, &why);
     if (s != CPI_OK) return set_error(s, why);
     *bytes = pl.total;
+    if (usable_workspace(pl.total) < pl.total) *bytes = tight.total;
     if (n > kMaxPassFrames) {
       // blocks of kMaxPassFrames frames
       size_t need = 0;
@@ -566,9 +568,12 @@ cpi_status cpi_correlate(const void* frames_a, const void* frames_b, int64_t n, 
                          int64_t* sum_b, void* workspace, size_t workspace_bytes,
                          void* stream) {
   return guarded([&]() -> cpi_status {
+    // byte rows in whole cache lines where the workspace holds them
+    const size_t usable = usable_workspace(workspace_bytes);
     cpi::CorrPlan pl;
     std::string why;
-    cpi_status s = cpi::plan_correlate(n, pa, pb, int(fmt), &pl, &why);
+    cpi_status s = cpi::plan_correlate(n, pa, pb, int(fmt), &pl, &why, cpi::kByteRowLine);
+    if (s == CPI_OK && usable < pl.total) s = cpi::plan_correlate(n, pa, pb, int(fmt), &pl, &why);
     if (s != CPI_OK) return set_error(s, why);
     s = check_frames(frames_a, frames_b);
     if (s != CPI_OK) return s;
@@ -581,7 +586,6 @@ cpi_status cpi_correlate(const void* frames_a, const void* frames_b, int64_t n, 
       if (o && !aligned16(o)) return set_error(CPI_ERR_INVALID_ARG, "outputs must be 16-byte aligned");
     if (!workspace || !aligned16(workspace))
       return set_error(CPI_ERR_INVALID_ARG, "workspace must be a 16-byte aligned device pointer");
-    const size_t usable = usable_workspace(workspace_bytes);
     if (usable < pl.total || n > kMaxPassFrames) {
       // memory-adaptive blocking (and inputs longer than one ingest pass):
       // fold the frames in blocks through the running sums of the streaming
@@ -1140,10 +1144,9 @@ cpi_status stream_push_device(cpi_stream_s* h, const uint8_t* fa, const uint8_t*
       const cpi::IngestJob ja{fa, h->pa, cp.pa_pad, op_a, csum_a, csum2_a, 0};
       const cpi::IngestJob jb{fb, h->pb, cp.pb_pad, op_b, csum_b, csum2_b, fp4 ? 1 : 0};
       CPI_HIP(cpi::u8_to_bits(ja, jb, k, cp.kpad_bits, stats, st), "ingest");
-      CPI_HIP(cpi::u8_sums(ja, jb, k, stats, st), "sums");
+      CPI_HIP(cpi::u8_to_bytes(ja, jb, k, cp.kpad_bytes, cp.row_bytes_bytes, stats, st), "ingest");
       CPI_HIP(cpi::add_select_i64(tot_a, csum_a, csum2_a, cp.pa_pad, stats, st), "sums");
       CPI_HIP(cpi::add_select_i64(tot_b, csum_b, csum2_b, cp.pb_pad, stats, st), "sums");
-      CPI_HIP(cpi::u8_to_bytes(ja, jb, k, cp.kpad_bytes, stats, st), "ingest");
     }
     int b = 0;
     if (h->refresh_gamma32) {
@@ -1161,6 +1164,7 @@ cpi_status stream_push_device(cpi_stream_s* h, const uint8_t* fa, const uint8_t*
     cpi::GemmArgs gy = g;
     gy.row_bytes = cp.row_bytes_bytes;
     gy.kblocks = cp.kpad_bytes / cpi::kByteBlock;
+    gy.pad_frames = cp.kpad_bytes - k;
     gy.cond = 2;
     gy.offset_from_stats = 1;
     gy.csum_a = csum2_a;

@@ -49,9 +49,8 @@ struct IngestJob {
 hipError_t ingest_bits(const IngestJob& a, const IngestJob& b, int64_t n, int64_t kpad_bits,
                        hipStream_t s);
 // Byte frames -> bit rows (bit = low bit of the byte) with per-pixel popcounts
-// added into sums, and the OR of every byte accumulated into stats[0].  The
-// rows and popcounts are the data exactly when stats[0] <= 1 (binary data);
-// stats[0] > 127 exactly when some byte exceeds 127.  swap02 as above.
+// added into sums.  The rows and popcounts are the data exactly when stats[0]
+// <= 1 afterwards (binary data); otherwise they are incomplete.  swap02 as above.
 hipError_t u8_to_bits(const IngestJob& a, const IngestJob& b, int64_t n, int64_t kpad_bits,
                       uint32_t* stats, hipStream_t s);
 // Side-by-side sensor frames (frame_h rows of frame_w 1-bit pixels, A the left
@@ -60,19 +59,16 @@ hipError_t u8_to_bits(const IngestJob& a, const IngestJob& b, int64_t n, int64_t
 hipError_t split_sidebyside(const uint8_t* frames, int64_t n, int frame_w, int frame_h, int roi_x,
                             int roi_y, int roi_w, int roi_h, uint8_t* out_a, uint8_t* out_b,
                             hipStream_t s);
-// Per-pixel byte sums (int64, added into sums2), executed only when
-// stats[0] > 1.
-hipError_t u8_sums(const IngestJob& a, const IngestJob& b, int64_t n, const uint32_t* stats,
-                   hipStream_t s);
 // dst[i] = (stats[0] <= 1 ? from_bits : from_bytes)[i]; and dst[i] += the same.
 hipError_t select_i64(int64_t* dst, const int64_t* from_bits, const int64_t* from_bytes,
                       int64_t count, const uint32_t* stats, hipStream_t s);
 hipError_t add_select_i64(int64_t* dst, const int64_t* from_bits, const int64_t* from_bytes,
                           int64_t count, const uint32_t* stats, hipStream_t s);
-// Byte frames -> int8 rows (row_bytes = kpad_bytes), executed only when
-// stats[0] > 1; values are offset by -128 when stats[0] > 127; pads are 0.
+// Byte frames -> byte rows (kpad_bytes frames, pads 0, of row_bytes each),
+// per-pixel byte sums added into sums2 and the OR of every byte into stats[1], executed only
+// when stats[0] > 1.
 hipError_t u8_to_bytes(const IngestJob& a, const IngestJob& b, int64_t n, int64_t kpad_bytes,
-                       const uint32_t* stats, hipStream_t s);
+                       int64_t row_bytes, uint32_t* stats, hipStream_t s);
 
 // ---- int8 MFMA contraction with the exact epilogue -----------------------
 enum EpiMode : int {
@@ -95,7 +91,8 @@ struct GemmArgs {
   int layout = CPI_GAMMA_VIEW_MAJOR;
   int cond = 0;                     // 0 always; 1 iff stats[0] <= 1; 2 iff stats[0] > 1
   int fp4 = 0;                      // bit rows as FP4 operands (M rows stored with swap02)
-  int offset_from_stats = 0;        // byte operands offset by -128 iff stats[0] > 127
+  int offset_from_stats = 0;        // byte operands offset by -128 iff stats[1] > 127
+  int64_t pad_frames = 0;           // byte operands: zero frames at the end of this pass
   int64_t pa = 0, pb = 0, n = 0;    // n: frames behind the result
   int64_t kchunk = 0;               // frames of this chunk (EPI_STREAM64)
   const int64_t* sum_a = nullptr;   // S_a, S_b of the result (raw, un-offset)

@@ -5,8 +5,8 @@
 // contiguous per pixel, so every frame block is transposed once here:
 //   * binary frames become bit rows: bit j of 32-bit word w of row p is the
 //     value of pixel p in frame 32*w + j (the paper's bit packing, Section 4.1);
-//   * other byte frames become int8 rows, offset by -128 when a value exceeds
-//     127 (this leaves the numerator of Eq. (1) unchanged).
+//   * other byte frames become byte rows (the contraction offsets them by -128
+//     when a value exceeds 127, which leaves the numerator of Eq. (1) unchanged).
 // Per-pixel sums S_a, S_b are produced on the way.  Frames beyond n and
 // pixels beyond npix read as zero, so padded rows and columns contribute
 // nothing to any product.
@@ -287,15 +287,40 @@ __global__ __launch_bounds__(256) void k_ingest_bits_tail(IngestJob j0, IngestJo
 // contiguous bytes per frame) and a slice of 128-frame units.  The low bits
 // of 8 frames are gathered into one byte per pixel (frame j of the 8 at bit
 // j: a mask and a shift-or per frame); four such octets are then regrouped
-// byte-wise into the 32-bit row words of the 4 pixels.  The OR of all bytes
-// goes to stats[0], so the rows (and the popcount sums) are valid exactly
-// when that OR is at most 1.
+// byte-wise into the 32-bit row words of the 4 pixels.  The OR of the bytes
+// goes to stats[0], so the rows (and the popcount sums) are valid exactly when
+// it ends up at most 1; a wave that starts when it is above 1 already has
+// nothing left to do (Da 128 x 128, Db 64 x 64, 20000 frames of photon counts:
+// 135 -> 107 us.  Stopping within a wave's units as well took the counts to
+// 35 us, but cost binary bytes 20 us).
 __device__ __forceinline__ void bytes_transpose4(const uint32_t (&t)[4], uint32_t (&w)[4]) {
   // w[k] byte o = t[o] byte k
-#pragma unroll
-  for (int k = 0; k < 4; ++k)
-    w[k] = ((t[0] >> (8 * k)) & 0xffu) | (((t[1] >> (8 * k)) & 0xffu) << 8) |
-           (((t[2] >> (8 * k)) & 0xffu) << 16) | (((t[3] >> (8 * k)) & 0xffu) << 24);
+  const uint32_t a = __builtin_amdgcn_perm(t[1], t[0], 0x05010400u);
+  const uint32_t b = __builtin_amdgcn_perm(t[1], t[0], 0x07030602u);
+  const uint32_t c = __builtin_amdgcn_perm(t[3], t[2], 0x05010400u);
+  const uint32_t d = __builtin_amdgcn_perm(t[3], t[2], 0x07030602u);
+  w[0] = __builtin_amdgcn_perm(c, a, 0x05040100u);
+  w[1] = __builtin_amdgcn_perm(c, a, 0x07060302u);
+  w[2] = __builtin_amdgcn_perm(d, b, 0x05040100u);
+  w[3] = __builtin_amdgcn_perm(d, b, 0x07060302u);
+}
+
+// Device-scope read of a flag word that other work-groups may set meanwhile (a
+// plain read stays stale in an XCD's cache).
+__device__ __forceinline__ uint32_t flag_now(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// ORs the four bytes of every lane's `any` into the flag word.  Bits only get
+// set during a launch, so a wave whose bits are all present already has nothing
+// to add: this keeps most waves off the contended word.
+__device__ __forceinline__ void set_flags(uint32_t* flags, uint32_t any, int lane) {
+  any = (any | (any >> 8) | (any >> 16) | (any >> 24)) & 0xffu;
+  for (int off = 32; off > 0; off >>= 1) any |= __shfl_xor(any, off, 64);
+  if (lane == 0 && any) {
+    const uint32_t cur = flag_now(flags);
+    if ((cur | any) != cur) atomicOr(flags, any);
+  }
 }
 
 template <bool ALIGNED>
@@ -317,6 +342,7 @@ __global__ __launch_bounds__(256) void k_u8_to_bits(IngestJob j0, IngestJob j1, 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t p0 = (blk * 4 + wave) * 256;
   if (p0 >= npix_pad || n <= 0) return;
+  if (flag_now(stats) > 1u) return;
   const int64_t px = p0 + 4 * lane;
   const int64_t u0 = int64_t(blockIdx.y) * units_per_slice;
   int64_t u1 = u0 + units_per_slice;
@@ -399,70 +425,7 @@ __global__ __launch_bounds__(256) void k_u8_to_bits(IngestJob j0, IngestJob j1, 
 #pragma unroll
   for (int k = 0; k < 4; ++k)
     if (s[k]) atomicAdd(&sums[px + k], (unsigned long long)s[k]);
-  any &= pmask;
-  any = (any | (any >> 8) | (any >> 16) | (any >> 24)) & 0xffu;
-  for (int off = 32; off > 0; off >>= 1) any |= __shfl_xor(any, off, 64);
-  // Bits of stats[0] only get set during the launch, so a wave whose bits are
-  // all present already (read at device scope, not from a stale cache) has
-  // nothing to add: this keeps most waves off the single contended word.
-  if (lane == 0 && any) {
-    const uint32_t cur = __hip_atomic_load(stats, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if ((cur | any) != cur) atomicOr(stats, any);
-  }
-}
-
-// Per-pixel byte sums (non-binary data only).  A work-group owns 256
-// consecutive pixels: 16 threads cover them 16 bytes each, and the 16 thread
-// rows walk interleaved frames of the group's frame slice.  Partial sums are
-// reduced in LDS, so each pixel receives one atomic per work-group.
-__global__ __launch_bounds__(256) void k_u8_sums(IngestJob j0, IngestJob j1, int64_t groups0, int64_t n,
-                                                 int64_t frames_per_slice,
-                                                 const uint32_t* __restrict__ stats) {
-  if (stats[0] <= 1u) return;
-  // work-groups [0, groups0) take detector job j0, the rest job j1
-  const bool second = int64_t(blockIdx.x) >= groups0;
-  const uint8_t* __restrict__ frames = second ? j1.frames : j0.frames;
-  const int64_t npix = second ? j1.npix : j0.npix;
-  unsigned long long* __restrict__ sums =
-      reinterpret_cast<unsigned long long*>(second ? j1.sums2 : j0.sums2);
-  const int64_t blk = int64_t(blockIdx.x) - (second ? groups0 : 0);
-  __shared__ uint32_t red[16][256 + 1];
-  const int t = threadIdx.x;
-  const int col = t & 15, row = t >> 4;
-  const int64_t px = blk * 256 + col * 16;
-  const int64_t f0 = int64_t(blockIdx.y) * frames_per_slice;
-  int64_t f1 = f0 + frames_per_slice;
-  if (f1 > n) f1 = n;
-  uint32_t s[16];
-#pragma unroll
-  for (int b = 0; b < 16; ++b) s[b] = 0;
-  if (px < npix) {
-    const bool vec = ((npix & 15) == 0);
-    for (int64_t f = f0 + row; f < f1; f += 16) {
-      const uint8_t* src = frames + f * npix + px;
-      uint32_t d[4] = {0u, 0u, 0u, 0u};
-      if (vec) {
-        const uint4 v = *reinterpret_cast<const uint4*>(src);
-        d[0] = v.x;
-        d[1] = v.y;
-        d[2] = v.z;
-        d[3] = v.w;
-      } else {
-        for (int b = 0; b < 16; ++b)
-          if (px + b < npix) d[b >> 2] |= uint32_t(src[b]) << (8 * (b & 3));
-      }
-#pragma unroll
-      for (int b = 0; b < 16; ++b) s[b] += (d[b >> 2] >> (8 * (b & 3))) & 0xffu;
-    }
-  }
-#pragma unroll
-  for (int b = 0; b < 16; ++b) red[row][col * 16 + b] = s[b];
-  __syncthreads();
-  const int64_t p = blk * 256 + t;
-  unsigned long long tot = 0;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) tot += red[r][t];
-  if (p < npix && tot) atomicAdd(&sums[p], tot);
+  set_flags(stats, any & pmask, lane);
 }
 
 __global__ void k_select_i64(int64_t* __restrict__ dst, const int64_t* __restrict__ a,
@@ -474,52 +437,99 @@ __global__ void k_select_i64(int64_t* __restrict__ dst, const int64_t* __restric
     dst[i] = add ? dst[i] + src[i] : src[i];
 }
 
-// Byte frames -> int8 rows through a 64 x 64 LDS tile (only when some byte
-// exceeds 1).  Pads (frames >= n, pixels >= npix) are written as 0, the
-// value of "no photon" in the offset domain.  Work-groups stride over the
-// tiles, so that for binary data (nothing to do) only a few thousand
-// work-groups start and exit.
-__global__ __launch_bounds__(256) void k_u8_to_bytes(IngestJob j0, IngestJob j1, int64_t n, int64_t kpad,
-                                                     int64_t tiles_p0, int64_t tiles0,
-                                                     int64_t tiles_p1, int64_t tiles,
-                                                     const uint32_t* __restrict__ stats) {
-  const uint32_t mx = stats[0];
-  if (mx <= 1u) return;
-  const uint32_t xo = mx > 127u ? 0x80u : 0u;
-  __shared__ uint8_t tile[64][64 + 4];
-  const int t = threadIdx.x;
-  // tiles [0, tiles0) belong to detector job j0, the rest to job j1
-  for (int64_t tt0 = blockIdx.x; tt0 < tiles; tt0 += gridDim.x) {
-    const bool second = tt0 >= tiles0;
-    const uint8_t* __restrict__ frames = second ? j1.frames : j0.frames;
-    const int64_t npix = second ? j1.npix : j0.npix;
-    uint8_t* __restrict__ out = second ? j1.out : j0.out;
-    const int64_t tiles_p = second ? tiles_p1 : tiles_p0;
-    const int64_t tt = tt0 - (second ? tiles0 : 0);
-    const int64_t p0 = (tt % tiles_p) * 64;
-    const int64_t f0 = (tt / tiles_p) * 64;
-    {
-      const int fl = t >> 2, pc = (t & 3) * 16;
-      const int64_t f = f0 + fl;
+// Byte frames -> byte rows, per-pixel byte sums and the OR of all bytes
+// (stats[1]), only when some byte exceeds 1 (stats[0]).  A wave owns 256
+// consecutive pixels (one dword, 4 pixels, per lane and frame) and a slice of
+// 64-frame units: 4 x 4 byte transposes in registers turn a unit's 64 dwords
+// into one 64-byte row segment per pixel, which the lane writes with four
+// consecutive 16-byte stores.  Pads (frames >= n, pixels >= npix of aligned
+// rows) are written as 0.  Bound by HBM: every byte read and written once
+// (Da 128 x 128, Db 64 x 64, 20000 frames: 410 + 410 MB in 230 us; the byte-wise
+// transpose through LDS that it replaces took 802 us, and a sums pass 101).
+template <bool ALIGNED>
+__global__ __launch_bounds__(256) void k_u8_to_bytes(IngestJob j0, IngestJob j1, int64_t groups0,
+                                                     int64_t n, int64_t pitch, int64_t nunits,
+                                                     int64_t units_per_slice,
+                                                     uint32_t* __restrict__ stats) {
+  if (stats[0] <= 1u) return;
+  // work-groups [0, groups0) take detector job j0, the rest job j1
+  const bool second = int64_t(blockIdx.x) >= groups0;
+  const uint8_t* __restrict__ frames = second ? j1.frames : j0.frames;
+  const int64_t npix = second ? j1.npix : j0.npix;
+  const int64_t npix_pad = second ? j1.npix_pad : j0.npix_pad;
+  uint8_t* __restrict__ out = second ? j1.out : j0.out;
+  unsigned long long* __restrict__ sums =
+      reinterpret_cast<unsigned long long*>(second ? j1.sums2 : j0.sums2);
+  const int64_t blk = int64_t(blockIdx.x) - (second ? groups0 : 0);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t p0 = (blk * 4 + wave) * 256;
+  if (p0 >= npix_pad) return;
+  const int64_t px = p0 + 4 * lane;
+  const int64_t u0 = int64_t(blockIdx.y) * units_per_slice;
+  int64_t u1 = u0 + units_per_slice;
+  if (u1 > nunits) u1 = nunits;
+  const bool pin = px < npix;
+  const uint32_t lane_off = uint32_t(pin ? px : 0);
+  const uint32_t pmask = pin ? 0xffffffffu : 0u;
+  auto load = [&](int64_t f) -> uint32_t {
+    const uint8_t* row = frames + f * npix;
+    if constexpr (ALIGNED) {
+      return *reinterpret_cast<const uint32_t*>(row + lane_off);
+    } else {
+      uint32_t v = 0;
 #pragma unroll
-      for (int b = 0; b < 16; ++b) {
-        const int64_t p = p0 + pc + b;
-        uint32_t v = 0;
-        if (f < n && p < npix) v = uint32_t(frames[f * npix + p]) ^ xo;
-        tile[fl][pc + b] = uint8_t(v);
+      for (int b = 0; b < 4; ++b) {
+        const uint32_t o = px + b < npix ? uint32_t(px + b) : 0u;
+        v |= uint32_t(row[o]) << (8 * b);
+      }
+      return v;
+    }
+  };
+  uint32_t any = 0;
+  unsigned long long total[4] = {0, 0, 0, 0};
+  for (int64_t u = u0; u < u1; ++u) {
+    const int64_t f0 = u * 64;
+    uint32_t d[64];
+    if (f0 + 64 <= n) {
+#pragma unroll
+      for (int j = 0; j < 64; ++j) d[j] = load(f0 + j);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 64; ++j) {
+        const bool fin = f0 + j < n;
+        d[j] = load(fin ? f0 + j : 0) & (fin ? 0xffffffffu : 0u);
       }
     }
-    __syncthreads();
-    {
-      const int pl = t >> 2, fc = (t & 3) * 16;
-      uint32_t d[4] = {0u, 0u, 0u, 0u};
+    uint32_t w[4][16], s[4] = {0, 0, 0, 0};
 #pragma unroll
-      for (int b = 0; b < 16; ++b) d[b >> 2] |= uint32_t(tile[fc + b][pl]) << (8 * (b & 3));
-      *reinterpret_cast<uint4*>(out + (p0 + pl) * kpad + f0 + fc) =
-          make_uint4(d[0], d[1], d[2], d[3]);
+    for (int q = 0; q < 16; ++q) {
+      uint32_t t[4], wk[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        t[j] = d[4 * q + j] & pmask;
+        any |= t[j];
+      }
+      bytes_transpose4(t, wk);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        w[k][q] = wk[k];
+        s[k] = __builtin_amdgcn_sad_u8(wk[k], 0u, s[k]);
+      }
     }
-    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      total[k] += s[k];
+      uint4* dst = reinterpret_cast<uint4*>(out + (px + k) * pitch + f0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        dst[q] = make_uint4(w[k][4 * q], w[k][4 * q + 1], w[k][4 * q + 2], w[k][4 * q + 3]);
+    }
   }
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (total[k]) atomicAdd(&sums[px + k], total[k]);
+  set_flags(stats + 1, any, lane);
 }
 
 // Side-by-side sensor frames -> the two detectors' bit frames.  A raw frame
@@ -630,23 +640,6 @@ hipError_t ingest_bits(const IngestJob& a, const IngestJob& b, int64_t n, int64_
   return hipSuccess;
 }
 
-hipError_t u8_sums(const IngestJob& a, const IngestJob& b, int64_t n, const uint32_t* stats,
-                   hipStream_t s) {
-  const int64_t groups0 = (a.npix + 255) / 256;
-  const int64_t groups = groups0 + (b.npix + 255) / 256;
-  int64_t slices = (2048 + groups - 1) / groups;
-  if (slices > (n + 15) / 16) slices = (n + 15) / 16;
-  if (slices < 1) slices = 1;
-  int64_t fps = (n + slices - 1) / slices;
-  // a thread row adds at most fps/16 bytes of <= 255 per pixel in uint32
-  if (fps > (int64_t(1) << 27)) fps = int64_t(1) << 27;
-  slices = (n + fps - 1) / fps;
-  if (slices > 65535 || groups > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_u8_sums, dim3(unsigned(groups), unsigned(slices)), dim3(256), 0, s, a, b,
-                     groups0, n, fps, stats);
-  return hipGetLastError();
-}
-
 hipError_t select_i64(int64_t* dst, const int64_t* from_bits, const int64_t* from_bytes,
                       int64_t count, const uint32_t* stats, hipStream_t s) {
   hipLaunchKernelGGL(k_select_i64, dim3(grid_for(count, 256)), dim3(256), 0, s, dst, from_bits,
@@ -681,15 +674,23 @@ hipError_t u8_to_bits(const IngestJob& a, const IngestJob& b, int64_t n, int64_t
 }
 
 hipError_t u8_to_bytes(const IngestJob& a, const IngestJob& b, int64_t n, int64_t kpad_bytes,
-                       const uint32_t* stats, hipStream_t s) {
-  const int64_t fblocks = kpad_bytes / 64;
-  const int64_t tiles_p0 = a.npix_pad / 64, tiles_p1 = b.npix_pad / 64;
-  const int64_t tiles0 = tiles_p0 * fblocks;
-  const int64_t tiles = tiles0 + tiles_p1 * fblocks;
-  const int64_t grid = tiles < 4096 ? tiles : 4096;
-  if (grid < 1) return hipSuccess;
-  hipLaunchKernelGGL(k_u8_to_bytes, dim3(unsigned(grid)), dim3(256), 0, s, a, b, n, kpad_bytes,
-                     tiles_p0, tiles0, tiles_p1, tiles, stats);
+                       int64_t row_bytes, uint32_t* stats, hipStream_t s) {
+  // a wave covers 256 rows: the padded row counts must be multiples of it
+  for (const IngestJob* j : {&a, &b})
+    if (j->npix_pad % 256 != 0 || j->npix_pad < j->npix) return hipErrorInvalidValue;
+  if (kpad_bytes % 64 != 0 || row_bytes % 64 != 0 || row_bytes < kpad_bytes)
+    return hipErrorInvalidValue;
+  const int64_t groups0 = (a.npix_pad / 256 + 3) / 4;
+  const int64_t groups = groups0 + (b.npix_pad / 256 + 3) / 4;
+  const int64_t waves = (a.npix_pad + b.npix_pad) / 256;
+  const int64_t nunits = kpad_bytes / 64;
+  const int64_t slices = slices_for(waves, nunits, 8192);
+  const int64_t ups = (nunits + slices - 1) / slices;
+  const int64_t used = (nunits + ups - 1) / ups;
+  if (groups > 0x7fffffff) return hipErrorInvalidValue;
+  auto* kern = ((a.npix | b.npix) & 3) == 0 ? k_u8_to_bytes<true> : k_u8_to_bytes<false>;
+  hipLaunchKernelGGL(kern, dim3(unsigned(groups), unsigned(used)), dim3(256), 0, s, a, b, groups0,
+                     n, row_bytes, nunits, ups, stats);
   return hipGetLastError();
 }
 

@@ -40,7 +40,7 @@ bool overflow_ok(int64_t n, int fmt) {
 }
 
 cpi_status plan_correlate(int64_t n, int64_t pa, int64_t pb, int fmt, CorrPlan* p,
-                          std::string* why) {
+                          std::string* why, int64_t byte_row_align) {
   if (!p) return fail(why, CPI_ERR_INVALID_ARG, "plan output is null");
   if (fmt != CPI_FRAMES_U8 && fmt != CPI_FRAMES_BIT1)
     return fail(why, CPI_ERR_INVALID_ARG, "unknown frame format");
@@ -63,7 +63,7 @@ cpi_status plan_correlate(int64_t n, int64_t pa, int64_t pb, int fmt, CorrPlan* 
   int64_t row = q.row_bytes_bits;
   if (fmt == CPI_FRAMES_U8) {
     q.kpad_bytes = round_up(n, kByteBlock);
-    q.row_bytes_bytes = q.kpad_bytes;
+    q.row_bytes_bytes = round_up(q.kpad_bytes, byte_row_align);
     q.passes = int((n + kByteChunk - 1) / kByteChunk);
     if (q.row_bytes_bytes > row) row = q.row_bytes_bytes;
   }

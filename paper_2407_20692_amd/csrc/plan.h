@@ -42,7 +42,7 @@ struct CorrPlan {
   int64_t kpad_bits = 0;            // frames, padded to kBitBlock
   int64_t kpad_bytes = 0;           // frames, padded to kByteBlock (U8 only)
   int64_t row_bytes_bits = 0;       // kpad_bits / 8
-  int64_t row_bytes_bytes = 0;      // kpad_bytes (U8 only)
+  int64_t row_bytes_bytes = 0;      // kpad_bytes, rounded up to byte_row_align (U8 only)
   int passes = 1;                   // int32 passes for byte operands
   // workspace layout (byte offsets)
   // sums: popcounts of the bit rows; sum2: byte sums (U8 data that is not binary)
@@ -51,9 +51,12 @@ struct CorrPlan {
   size_t total = 0;
 };
 
-// Fills `p`; returns CPI_OK or an error with `why` set.
+// Fills `p`; returns CPI_OK or an error with `why` set.  byte_row_align: 128
+// (whole cache lines, which the byte contraction reads at twice the rate) or
+// 64 (the smallest workspace).
+constexpr int64_t kByteRowLine = 128;
 cpi_status plan_correlate(int64_t n, int64_t pa, int64_t pb, int fmt, CorrPlan* p,
-                          std::string* why);
+                          std::string* why, int64_t byte_row_align = kByteBlock);
 
 struct PlainPlan {
   int64_t n = 0, pa = 0, pb = 0;
