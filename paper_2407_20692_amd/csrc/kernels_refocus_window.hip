@@ -15,9 +15,10 @@
 // weights come from one lane of each row of 16 by DPP: a DPP multiply-add in
 // index mode issues as fast as a plain one (measured: 256 of them 1193 clocks
 // against 1173, two waves per SIMD).  So a pair costs four multiply-adds and
-// 1.75 scalar instructions, and no LDS read.  Weights as scalar operands were
+// one scalar instruction, and no LDS read.  Weights as scalar operands were
 // slower: streamed through the scalar cache they arrive at one 64-byte line
-// in about 38 clocks per CU.
+// in about 38 clocks per CU.  The cells do come that way: a scalar register
+// holds two, as M0 takes them, so that a pair's index is one scalar move.
 //
 // LDS only hands the window over: a work-group (four waves, 256 (plane,
 // column) pairs, 128 view rows) copies the union of its waves' windows there
@@ -33,11 +34,15 @@
 // 16-pair chunks whose samples all fall outside the view are skipped.
 //
 // Measured, x pass and whole refocus: Da 256 x 256, Db 128 x 128, 128 planes
-// 18.8 -> 12.1 ms and 20.1 -> 13.3 ms; Da 128 x 128, Db 64 x 64, 32 planes 0.465 ->
-// 0.26 ms and 0.470 -> 0.31 ms; results bit-identical to k_ref_rows.  What is left
-// (large size): the multiply-adds alone take about 60% of the pass, and the
-// copies alone about 80%, as the work-groups of an XCD drift apart by more
-// views than its L2 holds and half of the copied lines miss it.
+// 18.8 -> 11.1 ms and 20.1 -> 12.4 ms; Da 128 x 128, Db 64 x 64, 32 planes 0.465 ->
+// 0.24 ms and 0.470 -> 0.29 ms; results bit-identical to k_ref_rows.  What is left
+// (large size): the multiply-adds take 6.5 ms of vector-ALU time; with two
+// waves per SIMD they overlap only in part with the scalar instructions (0.7
+// per multiply-add in all) and the hand-overs.  Without copies the pass takes
+// 10 ms.  Raising the priority of waves that multiply (the other wave of the
+// SIMD fills their gaps) gave 2%, whole-line copies of 32 columns nothing, and
+// reading the next window under the multiply-adds, into the half of the
+// registers that a narrow one leaves, nothing.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -57,8 +62,8 @@ constexpr int kWinBlocks = 9;        // 16-column blocks (8 KB each) that the LD
 constexpr int kWinBlockBytes = kWinSlots * 64 * 16 * 4;
 constexpr int kWinLds = kWinBlocks * kWinBlockBytes;
 constexpr int kWinMaxStages = 3;     // views staged at a time at most
-constexpr int kWinWaveWords = 160;   // table words per wave and view
-constexpr int kWinTabBytes = kWinWaves * kWinWaveWords * 4;
+constexpr int kWinWaveWords = 176;   // table words per wave and view
+constexpr int kWinTabBytes = kWinWaves * 512;   // of which the weights are staged in LDS
 constexpr int kWinMaxGroups = 64;    // plane groups per chunk (256 planes in groups of 4 or more)
 
 // Column cells of every pair of work-group (group gq, tile t) against
@@ -67,21 +72,23 @@ constexpr int kWinMaxGroups = 64;    // plane groups per chunk (256 planes in gr
 // table:
 //   words 0 .. 63 and 64 .. 127: weights w0 and w1, pair 16 k + i at word
 //     4 i + k (lane i of every row of 16 lanes reads the pairs it broadcasts);
-//   words 128 .. 143: one byte per pair, its cell's column in the wave's window;
-//   words 144 .. 150, of this view: where the wave's first four 4-column
-//     chunks start in the staged window (16-bit LDS offsets, to be exchanged
-//     (xor) with the lane's); its number of chunks and, from bit 8, one bit per
-//     16 pairs with a nonzero weight; the work-group's first staged column (a
-//     multiple of 4) and number of 16-column blocks staged;
-//   words 152 .. 156: the first three of the next view, and the last two of
-//     view x_b + 1 + stages (no blocks if there is none).
+//   words 128 .. 159: 16 bits per pair, what the VGPR index mode takes from M0:
+//     its cell's column in the wave's window, and the bit that puts the index on
+//     the second operand;
+//   words 160 .. 164: where the wave's first four 4-column chunks start in the
+//     staged window (16-bit LDS offsets, to be exchanged (xor) with the lane's);
+//     its number of chunks and, from bit 8, one bit per 16 pairs with a nonzero
+//     weight; the work-group's first staged column (a multiple of 4) and number
+//     of 16-column blocks staged;
+//   words 165 and 166: the last two of view x_b + ahead (no blocks if there is
+//     none).
 // Pairs past the planes or columns, or whose taps fall outside the view, have
 // zero weights.  One block per (gq, t, x_b).
 template <int NP, int XC, int PG>
 __global__ __launch_bounds__(256) void k_window_xtab(GeomI g, const int32_t* __restrict__ itab,
                                                      const float* __restrict__ ftab,
                                                      int64_t stride, int first, int count,
-                                                     int tiles, int max_blocks, int stages,
+                                                     int tiles, int max_blocks, int ahead,
                                                      int32_t* __restrict__ xe) {
   constexpr int CG = kWinWaves / PG;
   const int64_t idx = blockIdx.x;
@@ -139,7 +146,7 @@ __global__ __launch_bounds__(256) void k_window_xtab(GeomI g, const int32_t* __r
   const int slot = 4 * (k % 16) + k / 16;
   e[slot] = __builtin_bit_cast(int32_t, w0);
   e[64 + slot] = __builtin_bit_cast(int32_t, w1);
-  reinterpret_cast<uint8_t*>(e + 128)[k] = uint8_t(rel);
+  reinterpret_cast<uint16_t*>(e + 128)[k] = uint16_t(0x2000 | rel);
   if (k == 0) {
     int bits = 0;
 #pragma unroll
@@ -147,35 +154,30 @@ __global__ __launch_bounds__(256) void k_window_xtab(GeomI g, const int32_t* __r
     auto at = [](int q) { return uint32_t((q >> 2) * kWinBlockBytes | (q & 3) << 4); };
     const int xa = int(at(q0) | at(q0 + 1) << 16), xc = int(at(q0 + 2) | at(q0 + 3) << 16);
     const int nl = nq | bits << 8;
-    e[144] = xa;
-    e[145] = xc;
-    e[146] = nl;
-    e[147] = wx0;
-    e[148] = blocks;
-    if (xb > 0) {
-      int32_t* b = e - kStep;
-      b[152] = xa;
-      b[153] = xc;
-      b[154] = nl;
+    e[160] = xa;
+    e[161] = xc;
+    e[162] = nl;
+    e[163] = wx0;
+    e[164] = blocks;
+    if (xb >= ahead) {
+      int32_t* b = e - ahead * kStep;
+      b[165] = wx0;
+      b[166] = blocks;
     }
-    if (xb > stages) {
-      int32_t* b = e - (1 + stages) * kStep;
-      b[155] = wx0;
-      b[156] = blocks;
-    }
-    if (xb + 1 == g.wb) e[152] = e[153] = e[154] = 0;
-    if (xb + 1 + stages >= g.wb) e[155] = e[156] = 0;
+    if (xb + ahead >= g.wb) e[165] = e[166] = 0;
   }
 }
 
 // ---- one view of a wave, as one block of assembly --------------------------
 // The window lives in registers that only this block touches (40 for each of
 // the lane's two rows, from v168 and v208), and so do the weights (v248 .. v251
-// and v252 .. v255) and cells (v167): the block has to hold all of a view's
-// work.  That is the barrier after which the view's copies are in LDS, the
-// wave's reads of its window and table, the barrier after which the LDS space
-// is free, the copies of a later view into it, and the multiply-adds.  (M0 is
-// not restored: nothing else in the kernel uses it.)
+// and v252 .. v255): the block has to hold all of a view's work.  That is the
+// barrier after which the view's copies are in LDS and every wave has read the
+// view before it, the wave's reads of its window and weights, the copies of a
+// later view into the LDS space of the one before (a second barrier before
+// them where there is only one space), and the multiply-adds.  The cells come
+// through the scalar cache meanwhile, the next view's last words during the
+// multiply-adds.  (M0 is not restored: nothing else in the kernel uses it.)
 
 // waits until at most n copies of this wave are in flight: ever fewer, until
 // n allows as many
@@ -184,8 +186,7 @@ __global__ __launch_bounds__(256) void k_window_xtab(GeomI g, const int32_t* __r
   "s_cmp_ge_u32 %[fly], " #k "\n"  \
   "s_cbranch_scc1 Lwait%=\n"
 #define CPI_WIN_WAITS                                                                     \
-  CPI_WIN_WAIT(14) CPI_WIN_WAIT(12) CPI_WIN_WAIT(10) CPI_WIN_WAIT(9) CPI_WIN_WAIT(7)      \
-  CPI_WIN_WAIT(5) CPI_WIN_WAIT(3) CPI_WIN_WAIT(1)                                         \
+  CPI_WIN_WAIT(9) CPI_WIN_WAIT(7) CPI_WIN_WAIT(5) CPI_WIN_WAIT(3) CPI_WIN_WAIT(1)         \
   "s_waitcnt vmcnt(0)\n"                                                                  \
   "Lwait%=:\n"
 
@@ -231,97 +232,94 @@ __global__ __launch_bounds__(256) void k_window_xtab(GeomI g, const int32_t* __r
   CPI_WIN_COPY(7, 448) \
   CPI_WIN_COPY(8, 512)
 
-// the wave's table of the same view: 640 bytes, by 40 lanes
+// the wave's weights of the same view: 512 bytes, by 32 lanes
 #define CPI_WIN_TABLE                        \
   "s_mov_b32 m0, %[td]\n"                    \
-  "s_mov_b32 exec_hi, 0xff\n"                \
+  "s_mov_b32 exec_hi, 0\n"                   \
   "s_nop 0\n"                                \
   "global_load_lds_dwordx4 %[tl], %[tp]\n"   \
   "s_mov_b32 exec_hi, -1\n"
 
 // one pair: the sums of its two rows; lane i of every row of 16 lanes hands
-// its weights to the row (DPP), which costs a multiply-add nothing.  The
-// scalar instruction n goes between them.
+// its weights to the row (DPP), which costs a multiply-add nothing.
 #define CPI_WIN_DPP(a, w, v, i) \
   "v_fmac_f32_dpp %" #a ", " #w ", " #v " row_newbcast:" #i " row_mask:0xf bank_mask:0xf\n"
-#define CPI_WIN_PAIR(x, y, a, b, i, n)                           \
-  CPI_WIN_DPP(a, x, v168, i) n CPI_WIN_DPP(b, x, v208, i)        \
+#define CPI_WIN_PAIR(x, y, a, b, i)                              \
+  CPI_WIN_DPP(a, x, v168, i)   CPI_WIN_DPP(b, x, v208, i)        \
   CPI_WIN_DPP(a, y, v169, i) CPI_WIN_DPP(b, y, v209, i)
 // four pairs whose cells are the bytes of register c
-#define CPI_WIN_NEXT(c) "s_lshr_b32 " #c ", " #c ", 8\n"
-#define CPI_WIN_QUAD(c, x, y, a0, b0, i0, a1, b1, i1, a2, b2, i2, a3, b3, i3)        \
-  "s_set_gpr_idx_idx " #c "\n" CPI_WIN_PAIR(x, y, a0, b0, i0, CPI_WIN_NEXT(c))      \
-  "s_set_gpr_idx_idx " #c "\n" CPI_WIN_PAIR(x, y, a1, b1, i1, CPI_WIN_NEXT(c))      \
-  "s_set_gpr_idx_idx " #c "\n" CPI_WIN_PAIR(x, y, a2, b2, i2, CPI_WIN_NEXT(c))      \
-  "s_set_gpr_idx_idx " #c "\n" CPI_WIN_PAIR(x, y, a3, b3, i3, "")
+#define CPI_WIN_TWO(c, x, y, a0, b0, i0, a1, b1, i1)                  \
+  "s_mov_b32 m0, " #c "\n" CPI_WIN_PAIR(x, y, a0, b0, i0)             \
+  "s_lshr_b32 m0, " #c ", 16\n" CPI_WIN_PAIR(x, y, a1, b1, i1)
 #define CPI_WIN_CHUNK0 \
-  CPI_WIN_QUAD(s36, v248, v252, 0, 64, 0, 1, 65, 1, 2, 66, 2, 3, 67, 3) \
-  CPI_WIN_QUAD(s37, v248, v252, 4, 68, 4, 5, 69, 5, 6, 70, 6, 7, 71, 7) \
-  CPI_WIN_QUAD(s38, v248, v252, 8, 72, 8, 9, 73, 9, 10, 74, 10, 11, 75, 11) \
-  CPI_WIN_QUAD(s39, v248, v252, 12, 76, 12, 13, 77, 13, 14, 78, 14, 15, 79, 15)
+  CPI_WIN_TWO(s36, v248, v252, 0, 64, 0, 1, 65, 1) \
+  CPI_WIN_TWO(s37, v248, v252, 2, 66, 2, 3, 67, 3) \
+  CPI_WIN_TWO(s38, v248, v252, 4, 68, 4, 5, 69, 5) \
+  CPI_WIN_TWO(s39, v248, v252, 6, 70, 6, 7, 71, 7) \
+  CPI_WIN_TWO(s40, v248, v252, 8, 72, 8, 9, 73, 9) \
+  CPI_WIN_TWO(s41, v248, v252, 10, 74, 10, 11, 75, 11) \
+  CPI_WIN_TWO(s42, v248, v252, 12, 76, 12, 13, 77, 13) \
+  CPI_WIN_TWO(s43, v248, v252, 14, 78, 14, 15, 79, 15)
 #define CPI_WIN_CHUNK1 \
-  CPI_WIN_QUAD(s40, v249, v253, 16, 80, 0, 17, 81, 1, 18, 82, 2, 19, 83, 3) \
-  CPI_WIN_QUAD(s41, v249, v253, 20, 84, 4, 21, 85, 5, 22, 86, 6, 23, 87, 7) \
-  CPI_WIN_QUAD(s42, v249, v253, 24, 88, 8, 25, 89, 9, 26, 90, 10, 27, 91, 11) \
-  CPI_WIN_QUAD(s43, v249, v253, 28, 92, 12, 29, 93, 13, 30, 94, 14, 31, 95, 15)
+  CPI_WIN_TWO(s44, v249, v253, 16, 80, 0, 17, 81, 1) \
+  CPI_WIN_TWO(s45, v249, v253, 18, 82, 2, 19, 83, 3) \
+  CPI_WIN_TWO(s46, v249, v253, 20, 84, 4, 21, 85, 5) \
+  CPI_WIN_TWO(s47, v249, v253, 22, 86, 6, 23, 87, 7) \
+  CPI_WIN_TWO(s48, v249, v253, 24, 88, 8, 25, 89, 9) \
+  CPI_WIN_TWO(s49, v249, v253, 26, 90, 10, 27, 91, 11) \
+  CPI_WIN_TWO(s50, v249, v253, 28, 92, 12, 29, 93, 13) \
+  CPI_WIN_TWO(s51, v249, v253, 30, 94, 14, 31, 95, 15)
 #define CPI_WIN_CHUNK2 \
-  CPI_WIN_QUAD(s44, v250, v254, 32, 96, 0, 33, 97, 1, 34, 98, 2, 35, 99, 3) \
-  CPI_WIN_QUAD(s45, v250, v254, 36, 100, 4, 37, 101, 5, 38, 102, 6, 39, 103, 7) \
-  CPI_WIN_QUAD(s46, v250, v254, 40, 104, 8, 41, 105, 9, 42, 106, 10, 43, 107, 11) \
-  CPI_WIN_QUAD(s47, v250, v254, 44, 108, 12, 45, 109, 13, 46, 110, 14, 47, 111, 15)
+  CPI_WIN_TWO(s52, v250, v254, 32, 96, 0, 33, 97, 1) \
+  CPI_WIN_TWO(s53, v250, v254, 34, 98, 2, 35, 99, 3) \
+  CPI_WIN_TWO(s54, v250, v254, 36, 100, 4, 37, 101, 5) \
+  CPI_WIN_TWO(s55, v250, v254, 38, 102, 6, 39, 103, 7) \
+  CPI_WIN_TWO(s56, v250, v254, 40, 104, 8, 41, 105, 9) \
+  CPI_WIN_TWO(s57, v250, v254, 42, 106, 10, 43, 107, 11) \
+  CPI_WIN_TWO(s58, v250, v254, 44, 108, 12, 45, 109, 13) \
+  CPI_WIN_TWO(s59, v250, v254, 46, 110, 14, 47, 111, 15)
 #define CPI_WIN_CHUNK3 \
-  CPI_WIN_QUAD(s48, v251, v255, 48, 112, 0, 49, 113, 1, 50, 114, 2, 51, 115, 3) \
-  CPI_WIN_QUAD(s49, v251, v255, 52, 116, 4, 53, 117, 5, 54, 118, 6, 55, 119, 7) \
-  CPI_WIN_QUAD(s50, v251, v255, 56, 120, 8, 57, 121, 9, 58, 122, 10, 59, 123, 11) \
-  CPI_WIN_QUAD(s51, v251, v255, 60, 124, 12, 61, 125, 13, 62, 126, 14, 63, 127, 15)
+  CPI_WIN_TWO(s60, v251, v255, 48, 112, 0, 49, 113, 1) \
+  CPI_WIN_TWO(s61, v251, v255, 50, 114, 2, 51, 115, 3) \
+  CPI_WIN_TWO(s62, v251, v255, 52, 116, 4, 53, 117, 5) \
+  CPI_WIN_TWO(s63, v251, v255, 54, 118, 6, 55, 119, 7) \
+  CPI_WIN_TWO(s64, v251, v255, 56, 120, 8, 57, 121, 9) \
+  CPI_WIN_TWO(s65, v251, v255, 58, 122, 10, 59, 123, 11) \
+  CPI_WIN_TWO(s66, v251, v255, 60, 124, 12, 61, 125, 13) \
+  CPI_WIN_TWO(s67, v251, v255, 62, 126, 14, 63, 127, 15)
 #define CPI_WIN_SUM(c, CH)                    \
   "s_bitcmp1_b32 %[live], " #c "\n"           \
   "s_cbranch_scc0 Lskip" #c "%=\n" CH         \
   "Lskip" #c "%=:\n"
-#define CPI_WIN_CELLS \
-  "v_readlane_b32 s36, v167, 0\n" \
-  "v_readlane_b32 s37, v167, 1\n" \
-  "v_readlane_b32 s38, v167, 2\n" \
-  "v_readlane_b32 s39, v167, 3\n" \
-  "v_readlane_b32 s40, v167, 4\n" \
-  "v_readlane_b32 s41, v167, 5\n" \
-  "v_readlane_b32 s42, v167, 6\n" \
-  "v_readlane_b32 s43, v167, 7\n" \
-  "v_readlane_b32 s44, v167, 8\n" \
-  "v_readlane_b32 s45, v167, 9\n" \
-  "v_readlane_b32 s46, v167, 10\n" \
-  "v_readlane_b32 s47, v167, 11\n" \
-  "v_readlane_b32 s48, v167, 12\n" \
-  "v_readlane_b32 s49, v167, 13\n" \
-  "v_readlane_b32 s50, v167, 14\n" \
-  "v_readlane_b32 s51, v167, 15\n"
 
 #define CPI_WIN_VIEW                                     \
+  "s_load_dwordx16 s[36:51], %[th], 512\n"               \
+  "s_load_dwordx16 s[52:67], %[th], 576\n"               \
   CPI_WIN_WAITS                                          \
   "s_barrier\n"                                          \
-  "ds_read_b32 v167, %[tc]\n"                            \
   "ds_read_b128 v[248:251], %[tw]\n"                     \
   "ds_read_b128 v[252:255], %[tw] offset:256\n"          \
   CPI_WIN_READS                                          \
   "Lread%=:\n"                                           \
+  "s_cmp_eq_u32 %[spaces], 1\n"                            \
+  "s_cbranch_scc0 Ltwo%=\n"                              \
   "s_waitcnt lgkmcnt(0)\n"                               \
   "s_barrier\n"                                          \
+  "Ltwo%=:\n"                                            \
   CPI_WIN_COPIES                                         \
   "Lcopy%=:\n"                                           \
   CPI_WIN_TABLE                                          \
-  "v_readlane_b32 %[xa], v167, 24\n"                     \
-  "v_readlane_b32 %[xc], v167, 25\n"                     \
-  "v_readlane_b32 %[nl], v167, 26\n"                     \
-  "v_readlane_b32 %[wx], v167, 27\n"                     \
-  "v_readlane_b32 %[nw], v167, 28\n"                     \
-  CPI_WIN_CELLS                                          \
-  "s_nop 3\n"                                            \
+  "s_waitcnt lgkmcnt(0)\n"                               \
+  "s_load_dwordx8 s[68:75], %[tn], 640\n"                \
+  "s_setprio 2\n"                                        \
   "s_set_gpr_idx_on s36, 2\n"                            \
   CPI_WIN_SUM(0, CPI_WIN_CHUNK0)                         \
   CPI_WIN_SUM(1, CPI_WIN_CHUNK1)                         \
   CPI_WIN_SUM(2, CPI_WIN_CHUNK2)                         \
   CPI_WIN_SUM(3, CPI_WIN_CHUNK3)                         \
-  "s_set_gpr_idx_off\n"
+  "s_set_gpr_idx_off\n"                                  \
+  "s_setprio 0\n"                                  \
+  "s_waitcnt lgkmcnt(0)\n"
 
 #define CPI_WIN_ACC \
   "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]), \
@@ -352,17 +350,19 @@ __global__ __launch_bounds__(256) void k_window_xtab(GeomI g, const int32_t* __r
       "+v"(acc[127])
 #define CPI_WIN_CLOBBERS \
   "s36", "s37", "s38", "s39", "s40", "s41", "s42", "s43", "s44", "s45", "s46", "s47", "s48", \
-      "s49", "s50", "s51", "v167", "v168", "v169", "v170", "v171", "v172", "v173", "v174", \
-      "v175", "v176", "v177", "v178", "v179", "v180", "v181", "v182", "v183", "v184", "v185", \
-      "v186", "v187", "v188", "v189", "v190", "v191", "v192", "v193", "v194", "v195", "v196", \
-      "v197", "v198", "v199", "v200", "v201", "v202", "v203", "v204", "v205", "v206", "v207", \
-      "v208", "v209", "v210", "v211", "v212", "v213", "v214", "v215", "v216", "v217", "v218", \
-      "v219", "v220", "v221", "v222", "v223", "v224", "v225", "v226", "v227", "v228", "v229", \
-      "v230", "v231", "v232", "v233", "v234", "v235", "v236", "v237", "v238", "v239", "v240", \
-      "v241", "v242", "v243", "v244", "v245", "v246", "v247", "v248", "v249", "v250", "v251", \
-      "v252", "v253", "v254", "v255", "scc", "memory"
+      "s49", "s50", "s51", "s52", "s53", "s54", "s55", "s56", "s57", "s58", "s59", "s60", \
+      "s61", "s62", "s63", "s64", "s65", "s66", "s67", "v168", "v169", "v170", "v171", \
+      "v172", "v173", "v174", "v175", "v176", "v177", "v178", "v179", "v180", "v181", "v182", \
+      "v183", "v184", "v185", "v186", "v187", "v188", "v189", "v190", "v191", "v192", "v193", \
+      "v194", "v195", "v196", "v197", "v198", "v199", "v200", "v201", "v202", "v203", "v204", \
+      "v205", "v206", "v207", "v208", "v209", "v210", "v211", "v212", "v213", "v214", "v215", \
+      "v216", "v217", "v218", "v219", "v220", "v221", "v222", "v223", "v224", "v225", "v226", \
+      "v227", "v228", "v229", "v230", "v231", "v232", "v233", "v234", "v235", "v236", "v237", \
+      "v238", "v239", "v240", "v241", "v242", "v243", "v244", "v245", "v246", "v247", "v248", \
+      "v249", "v250", "v251", "v252", "v253", "v254", "v255", "scc", "memory"
 
 typedef int i4v __attribute__((ext_vector_type(4)));
+typedef int i8v __attribute__((ext_vector_type(8)));
 
 // (read through the scalar cache: the kernel does not write the tables)
 typedef const __attribute__((address_space(4))) int32_t* TabPtr;
@@ -437,8 +437,8 @@ __global__ __launch_bounds__(64 * kWinWaves, 2) void k_ref_window(
     const uint32_t j1 = uint32_t(64 * g.wa);   // 16 rows down
     const uint32_t base = uint32_t(reinterpret_cast<uintptr_t>(ring));
     const uint32_t rd = uint32_t(64 * (lane & 15) + 1024 * (lane >> 4) + 16 * ((lane >> 2) & 3));
-    const uint32_t tl = uint32_t(16 * (lane < 40 ? lane : 0));
-    const uint32_t tab0 = base + uint32_t(kWinLds + wave * kWinWaveWords * 4);
+    const uint32_t tl = uint32_t(16 * (lane & 31));
+    const uint32_t tab0 = base + uint32_t(kWinLds + wave * 512);
     constexpr int kStep = kWinWaves * kWinWaveWords;
     const int32_t* tp = xe + (int64_t(gq * tiles + t) * g.wb * kWinWaves + wave) * kWinWaveWords;
     TabPtr th = (TabPtr)tp;
@@ -448,13 +448,13 @@ __global__ __launch_bounds__(64 * kWinWaves, 2) void k_ref_window(
       const uint64_t a = reinterpret_cast<uint64_t>(view + wx0);
       return i4v{int(uint32_t(a)), int(uint32_t(a >> 32) & 0xffffu), (pa - wx0) * 4, 0x00020000};
     };
-    // the first `stages` views' copies; f1 and f2: the copies started by the
-    // last and the last but one view
-    int f1 = 0, f2 = 0;
-    for (int k = 0; k < stages; ++k) {
+    // the copies of the first `ahead` views
+    const int ahead = stages == 1 ? 1 : stages - 1;
+    int f1 = 0;   // copies started last
+    for (int k = 0; k < ahead; ++k) {
       const int kk = k < last ? k : last;
-      const i4v rs = desc(th[kk * kStep + 147]);
-      const int nb = mine && k <= last ? th[kk * kStep + 148] : 0;
+      const i4v rs = desc(th[kk * kStep + 163]);
+      const int nb = mine && k <= last ? th[kk * kStep + 164] : 0;
       // (s_nop: a descriptor register may just have been written by a vector
       // instruction)
       asm volatile("s_nop 4\n" CPI_WIN_COPIES "Lcopy%=:\n" CPI_WIN_TABLE
@@ -464,51 +464,44 @@ __global__ __launch_bounds__(64 * kWinWaves, 2) void k_ref_window(
                      [td] "s"(tab0 + uint32_t(k * kWinTabBytes)), [tl] "v"(tl),
                      [tp] "s"(tp + kk * kStep)
                    : "scc", "memory");
-      f2 = f1;
       f1 = 2 * nb + 1;
       if (k < last) view += pa;
     }
-    // scalar words one view ahead of their use: this wave's chunks, and the
-    // copies that start during the view
-    int xa = th[144], xc = th[145], nl = th[146], wx = 0, nw = 0;
-    if (stages <= last) {
-      wx = th[stages * kStep + 147];
-      nw = th[stages * kStep + 148];
-    }
-    tp += int64_t(stages <= last ? stages : last) * kStep;
-    int stage = 0;
+    i8v head;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) head[k] = th[160 + k];
+    tp += int64_t(ahead <= last ? ahead : last) * kStep;
+    int stage = 0, to = ahead % stages;   // of this view, and of the copies it starts
 #pragma unroll 1
     for (int v = 0; v <= last; ++v) {
-      const int fly = (stages > 1 ? f1 : 0) + (stages > 2 ? f2 : 0);
-      const i4v rs = desc(wx);
-      const int nb = mine ? nw : 0;
-      const int nq = nl & 0xff, live = nl >> 8;
+      TabPtr tn = v < last ? th + kStep : th;
+      const int fly = ahead > 1 ? f1 : 0;
+      const i4v rs = desc(head[5]);
+      const int nb = mine ? head[6] : 0;
+      const int xa = head[0], xc = head[1];
+      const int nq = head[2] & 0xff, live = head[2] >> 8;
       const uint32_t sb = base + uint32_t(stage * stage_bytes);
-      const uint32_t td = tab0 + uint32_t(stage * kWinTabBytes);
       const uint32_t a0 = (rd ^ uint32_t(xa & 0xffff)) + sb;
       const uint32_t a1 = (rd ^ (uint32_t(xa) >> 16)) + sb;
       const uint32_t a2 = (rd ^ uint32_t(xc & 0xffff)) + sb;
       const uint32_t a3 = (rd ^ (uint32_t(xc) >> 16)) + sb;
-      const uint32_t tc = td + uint32_t(512 + 4 * (lane & 31));
-      const uint32_t tw = td + uint32_t(16 * (lane & 15));
-      int nxa, nxc, nnl, nwx, nnw;
+      const uint32_t tw = tab0 + uint32_t(stage * kWinTabBytes) + uint32_t(16 * (lane & 15));
+      i8v next;
       asm volatile(CPI_WIN_VIEW
-                   : CPI_WIN_ACC, [xa] "=&s"(nxa), [xc] "=&s"(nxc), [nl] "=&s"(nnl),
-                     [wx] "=&s"(nwx), [nw] "=&s"(nnw)
-                   : [fly] "s"(fly), [nq] "s"(nq), [nb] "s"(nb), [dst] "s"(sb + 2048 * wave),
-                     [rs] "s"(rs), [live] "s"(live), [a0] "v"(a0), [a1] "v"(a1), [a2] "v"(a2),
-                     [a3] "v"(a3), [from] "v"(from), [j1] "s"(j1), [td] "s"(td), [tl] "v"(tl),
-                     [tp] "s"(tp), [tc] "v"(tc), [tw] "v"(tw)
+                   : CPI_WIN_ACC, [next] "=&{s[68:75]}"(next)
+                   : [fly] "s"(fly), [nq] "s"(nq), [nb] "s"(nb), [spaces] "s"(stages),
+                     [dst] "s"(base + uint32_t(to * stage_bytes + 2048 * wave)), [rs] "s"(rs),
+                     [live] "s"(live), [a0] "v"(a0), [a1] "v"(a1), [a2] "v"(a2), [a3] "v"(a3),
+                     [from] "v"(from), [j1] "s"(j1),
+                     [td] "s"(tab0 + uint32_t(to * kWinTabBytes)), [tl] "v"(tl), [tp] "s"(tp),
+                     [th] "s"(th), [tn] "s"(tn), [tw] "v"(tw)
                    : CPI_WIN_CLOBBERS);
-      xa = nxa;
-      xc = nxc;
-      nl = nnl;
-      wx = nwx;
-      nw = nnw;
-      f2 = f1;
+      head = next;
+      th = tn;
       f1 = 2 * nb + 1;
       stage = stage + 1 == stages ? 0 : stage + 1;
-      if (v + stages < last) {
+      to = to + 1 == stages ? 0 : to + 1;
+      if (v + ahead < last) {
         view += pa;
         tp += kStep;
       }
@@ -555,7 +548,6 @@ __global__ __launch_bounds__(64 * kWinWaves, 2) void k_ref_window(
 #undef CPI_WIN_TABLE
 #undef CPI_WIN_DPP
 #undef CPI_WIN_SUM
-#undef CPI_WIN_CELLS
 #undef CPI_WIN_CHUNK2
 #undef CPI_WIN_CHUNK3
 #undef CPI_WIN_WAIT
@@ -565,8 +557,7 @@ __global__ __launch_bounds__(64 * kWinWaves, 2) void k_ref_window(
 #undef CPI_WIN_COPY
 #undef CPI_WIN_COPIES
 #undef CPI_WIN_PAIR
-#undef CPI_WIN_NEXT
-#undef CPI_WIN_QUAD
+#undef CPI_WIN_TWO
 #undef CPI_WIN_CHUNK0
 #undef CPI_WIN_CHUNK1
 #undef CPI_WIN_VIEW
@@ -665,7 +656,7 @@ hipError_t launch_window(const float* gamma, const RefGeom& g, const double* alp
   const int stages = std::min(kWinMaxStages, kWinBlocks / blocks);
   if (nwg > 0x7fffffff) return hipErrorInvalidValue;
   hipLaunchKernelGGL((k_window_xtab<NP, XC, PG>), dim3(unsigned(nx)), dim3(256), 0, s, gi, itab,
-                     ftab, stride, first, count, tiles, blocks, stages, xe);
+                     ftab, stride, first, count, tiles, blocks, stages == 1 ? 1 : stages - 1, xe);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_ref_window<NP, XC, PG>), dim3(unsigned(nwg)), dim3(64 * kWinWaves), 0, s,

@@ -46,3 +46,19 @@ def test_window_edges(i):
     got = _run(cpi, cpi.refocus, gam32, g, al)
     assert_r12(got, want, i)
     assert np.array_equal(got, _run(cpi, cpi.refocus, gam32, g, al)), i
+
+
+@pytest.mark.parametrize("wb", [1, 2, 3, 8])
+@pytest.mark.parametrize("lo,hi", [(0.5, 0.52), (0.8, 0.82), (0.97, 1.03)])
+def test_window_stages(lo, hi, wb):
+    """Windows of which the LDS holds three, two or one, over as many views,
+    fewer and more."""
+    import paper_2407_20692_amd as cpi
+    g, al = _geo(128, 66, wb, 6), np.linspace(lo, hi, 4)
+    rng = np.random.default_rng(int(1000 * lo) + wb)
+    gam32 = rng.standard_normal((g.hb * g.wb, g.ha * g.wa)).astype(np.float32)
+    want = oracle.refocus(gam32.astype(np.float64), g, al)
+    log(f"case stages {lo} {hi} {wb}")
+    got = _run(cpi, cpi.refocus, gam32, g, al)
+    assert_r12(got, want, 0)
+    assert np.array_equal(got, _run(cpi, cpi.refocus, gam32, g, al))
