@@ -25,11 +25,15 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float(uint32_t(h) << 16); }
 
-// Round to nearest even; NaN stays a (quiet) NaN.
-__device__ __forceinline__ uint16_t f2bf(float f) {
-  const uint32_t u = __float_as_uint(f);
-  if ((u & 0x7FFFFFFFu) > 0x7F800000u) return uint16_t((u >> 16) | 0x40u);
-  return uint16_t((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
+// Round to nearest even; NaN stays a (quiet) NaN.  (One instruction; over all
+// 2^32 inputs the same as (u + 0x7FFF + (u >> 16 & 1)) >> 16, and u >> 16 | 0x40
+// for NaN.)
+__device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, __bf16(f)); }
+// two floats, a in the low half
+__device__ __forceinline__ uint32_t pack_bf(float a, float b) {
+  typedef float v2f __attribute__((ext_vector_type(2)));
+  typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v2f{a, b}, v2bf));
 }
 
 // 2x2 max-pooling of 8 channels: elementwise maximum of the four 16-byte
@@ -169,23 +173,79 @@ __global__ __launch_bounds__(256) void k_conv(NnConvArgs a) {
 // (WM x WN); wave (wm, wn) owns rows [wm*TM, (wm+1)*TM) (one 16-pixel
 // fragment per row) and channels [wn*16*TN, (wn+1)*16*TN).  Per chunk of 32
 // input channels the block's input pixels with their one-pixel halo
-// ((TH + 2) x 18 pixels) are staged in LDS once; per phase of KY kernel rows
-// (KY = 1 or 3) the weights of their taps for the NT channels are staged
-// beside them, and those taps run from LDS.  Pixel and weight rows are padded
-// to 40 elements (80 bytes) to spread LDS banks.
+// ((TH + 2) x 18 pixels) and the nine taps' weights for the NT channels are
+// staged in LDS, and the taps run from there.
+//
+// Staging goes from memory to LDS directly, no registers between, pixels
+// outside the image as out-of-range lanes, which deliver zeros.  A chunk has
+// three phases, one per kernel row, each behind one barrier: after the one of
+// phase 0 every wave reads all its pixel fragments (a row serves up to three
+// kernel rows), and what a barrier shows to be read by all is refilled for the
+// next chunk, the weights of kernel row k and, from phase 1, the pixels, so
+// that copies have two phases to arrive.
+//
+// LDS layout: 64 bytes per pixel or weight row; piece c (16 bytes) of row p at
+// c ^ 2 (p / 4 % 2).  A 16-byte read of 64 lanes (rows p .. p + 15, piece
+// lane / 16) is served in groups of 16 lanes (0-3, 12-15, 20-27 and their
+// complement, and so again from 32); each covers all banks once, whatever p is.
+// Pixel rows are 20 pixels apart, an odd number of fours: the exchange of a
+// lane's pieces alternates from row to row.
+//
+// What bounds it: latency.  A layer of batch 32 (64 x 64 pixels, 64 channels)
+// takes 8 us of matrix-core time and 7 us for its activations at the rate of a
+// large copy, but a work-group has only one to six chunks to run, so address
+// arithmetic, waits and the epilogue count.  Times of a layer's launch (its
+// start of about 4 us included): 29 -> 18 us; with 32 channels at 128 x 128,
+// 33 -> 21 us; the concatenated inputs (128 and 64 channels) 50 -> 32 and
+// 60 -> 34 us, against staging through registers, with branches and 64-bit
+// addresses per piece, rows padded to 80 bytes (three of 16 lanes in conflict)
+// and each pixel fragment read once per tap.
+constexpr int kHaloPitch = 20;
+
+typedef __attribute__((address_space(3))) uint8_t* nn_lds_t;
+
+// LDS-direct copy of 16 bytes per lane to 1 KB from dst; an offset at or above
+// 2^31 delivers zeros
+__device__ __forceinline__ void copy_lds16(__amdgpu_buffer_rsrc_t from, uint8_t* dst,
+                                           uint32_t voff, uint32_t soff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(from, (nn_lds_t)dst, 16, int(voff), int(soff), 0, 0);
+}
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* p) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, 0x7fffffff, 0x00020000);
+}
+
+// waits until at most n of this wave's copies are in flight
+template <int N>
+__device__ __forceinline__ void nn_wait_copies() {
+  static_assert(N >= 0 && N < 64, "");
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | (N >> 4) << 14);
+}
+// waits until this wave's LDS reads and writes are done
+__device__ __forceinline__ void nn_wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void nn_barrier() {
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// the value of the lane whose number differs in bit 0
+__device__ __forceinline__ float nn_swap_lanes(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xf, 0xf, true));   // quad_perm 1 0 3 2
+}
+
 // MODE: 0 input and output as stored; 1 input read through the 2x2
 // max-pool; 2 output split (dlow / dskip); 3 input concatenated (low).
-template <int TM, int TN, int WM, int WN, int KY, int MODE>
-__global__ __launch_bounds__(256) void k_conv3_lds(NnConvArgs a) {
+template <int TM, int TN, int WM, int WN, int MODE>
+__device__ __forceinline__ void conv3_lds(const NnConvArgs& a, uint8_t* lds) {
   constexpr bool POOL = MODE == 1, SPLIT = MODE == 2, CAT = MODE == 3;
   constexpr int TH = WM * TM, TW = 16, NT = WN * TN * 16;
-  constexpr int HW = TW + 2, HH = TH + 2;
-  constexpr int PITCH = 40;  // elements per staged pixel / weight row
-  static_assert(KY == 1 || KY == 3, "kernel rows per phase");
-  __shared__ __attribute__((aligned(16))) uint16_t halo[HH * HW * PITCH];
-  __shared__ __attribute__((aligned(16))) uint16_t slab[3 * KY * NT * PITCH];
+  constexpr int HW = kHaloPitch, HH = TH + 2;
+  constexpr int HC = (HH * HW + 15) / 16, HI = (HC + 3) / 4;   // halo copies, per wave at most
+  constexpr int SC = 3 * NT / 16, SI = (SC + 3) / 4;           // and of a kernel row's weights
+  constexpr int HL = POOL ? 0 : HC / 4, SL = SC / 4;           // per wave at least
   const int t = threadIdx.x;
-  const int lane = t & 63, wave = t >> 6;
+  const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int r = lane & 15, g = lane >> 4;
   const int wm = wave / WN, wn = wave % WN;
   const int cols = (a.W + TW - 1) / TW, rows = (a.H + TH - 1) / TH;
@@ -197,123 +257,141 @@ __global__ __launch_bounds__(256) void k_conv3_lds(NnConvArgs a) {
   const int x0 = bx * TW, y0 = by * TH;
   const int n0 = blockIdx.y * NT;
   const int Cin = a.Cin;
+  uint8_t* halo = lds;
+  uint8_t* slab = lds + HC * 1024;   // kernel row k from SC * 1024 k
+
+  // Copies: 16 pixels or weight rows x 64 bytes each, wave w takes copies w,
+  // w + 4, ...; lane l writes slot l, of row l / 4.  Offsets are from the first
+  // row (of the image, or of the half-resolution one) that the block sees.
   // input channels [0, c_low) from the upsampled low-resolution tensor, the
   // rest from in (c_low = 0: all from in)
   const int Cs = Cin - a.c_low, Wl = a.W / 2;
-  const uint16_t* img = a.in + int64_t(b) * a.H * a.W * Cs;
-  const uint16_t* limg = a.low ? a.low + int64_t(b) * (a.H / 2) * Wl * a.c_low : nullptr;
+  const int piece = (lane & 3) ^ ((lane >> 4 & 1) << 1);
+  uint32_t hoff[HI], loff[CAT ? HI : 1];
+  if constexpr (!POOL) {
+#pragma unroll
+    for (int u = 0; u < HI; ++u) {
+      const int px = 16 * (wave + 4 * u) + (lane >> 2);
+      const int hy = px / HW, hx = px - hy * HW;
+      const int yy = y0 + hy - 1, xx = x0 + hx - 1;
+      const bool in = hy < HH && hx < TW + 2 && yy >= 0 && yy < a.H && xx >= 0 && xx < a.W;
+      hoff[u] = in ? uint32_t(((hy - 1) * a.W + xx) * Cs + 8 * piece + a.W * Cs) * 2 : 0x80000000u;
+      if constexpr (CAT)
+        loff[u] = in ? uint32_t(((yy >> 1) - (y0 >> 1) + 1) * Wl + (xx >> 1)) * a.c_low * 2 +
+                           16 * piece
+                     : 0x80000000u;
+    }
+  }
+  const auto rin = buffer_at(a.in + (int64_t(b) * a.H + y0 - 1) * a.W * Cs);
+  const auto rlow =
+      CAT ? buffer_at(a.low + (int64_t(b) * (a.H / 2) + (y0 >> 1) - 1) * Wl * a.c_low) : rin;
+  const auto rwk = buffer_at(a.wk + int64_t(n0) * a.Kpad);
+  const uint32_t woff = uint32_t((lane >> 2) * a.Kpad + 8 * piece) * 2;
+  auto copy_halo = [&](int c0) {
+    if constexpr (POOL) {
+#pragma unroll 2
+      for (int q = t; q < HH * HW * 4; q += 256) {
+        const int px = q >> 2, part = q & 3;
+        const int hy = px / HW, hx = px % HW;
+        const int yy = y0 + hy - 1, xx = x0 + hx - 1;
+        uint4 v = make_uint4(0, 0, 0, 0);
+        if (hx < TW + 2 && yy >= 0 && yy < a.H && xx >= 0 && xx < a.W)
+          v = pool4(a.in + ((int64_t(b) * 2 * a.H + 2 * yy) * 2 * a.W + 2 * xx) * Cin + c0 +
+                        8 * part,
+                    Cin, int64_t(2) * a.W * Cin);
+        *reinterpret_cast<uint4*>(halo + 64 * px + 16 * (part ^ ((px >> 2 & 1) << 1))) = v;
+      }
+    } else {
+      const bool low = CAT && c0 < a.c_low;
+#pragma unroll
+      for (int u = 0; u < HI; ++u)
+        if (HC % 4 == 0 || u + 1 < HI || wave < HC % 4) {
+          uint8_t* dst = halo + 1024 * (wave + 4 * u);
+          if (low)
+            copy_lds16(rlow, dst, loff[CAT ? u : 0], uint32_t(2 * c0));
+          else
+            copy_lds16(rin, dst, hoff[u], uint32_t(2 * (c0 - a.c_low)));
+        }
+    }
+  };
+  auto copy_slab = [&](int c0, int ky) {   // row of kernel row ky: kx * NT + n
+#pragma unroll
+    for (int u = 0; u < SI; ++u)
+      if (SC % 4 == 0 || u + 1 < SI || wave < SC % 4) {
+        const int k = wave + 4 * u, kx = k / (NT / 16), n = k % (NT / 16) * 16;
+        copy_lds16(rwk, slab + (SC * ky + k) * 1024, woff,
+                   uint32_t(n * a.Kpad + (3 * ky + kx) * Cin + c0) * 2);
+      }
+  };
 
   v4f acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = v4f{0, 0, 0, 0};
+  // lane's addresses of the first halo row's fragments, and of even weight rows
+  const uint8_t* hp[3];
+#pragma unroll
+  for (int kx = 0; kx < 3; ++kx) {
+    const int px = wm * TM * HW + r + kx;
+    hp[kx] = halo + 64 * px + 16 * (g ^ ((px >> 2 & 1) << 1));
+  }
+  const uint8_t* sp = slab + 64 * (wn * 16 * TN + r) + 16 * (g ^ ((r >> 2 & 1) << 1));
 
-  // Phases p = (3 / KY) * chunk + kernel-row group.  The global loads of
-  // phase p + 1 (the halo when a new chunk starts, and the weight slab) are
-  // issued into registers before the matrix-core ops of phase p and written
-  // to LDS after them.
-  constexpr int PPC = 3 / KY;                          // phases per chunk
-  constexpr int HQ = (HH * HW * 4 + 255) / 256;        // halo pieces per thread
-  constexpr int SQ = (3 * KY * NT * 4 + 255) / 256;    // slab pieces per thread
-  uint4 hreg[HQ], sreg[SQ];
-  auto load_halo = [&](int c0) {
-#pragma unroll
-    for (int u = 0; u < HQ; ++u) {
-      const int q = t + 256 * u;
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (q < HH * HW * 4) {
-        const int px = q >> 2, part = q & 3;
-        const int hy = px / HW, hx = px % HW;
-        const int yy = y0 + hy - 1, xx = x0 + hx - 1;
-        if (yy >= 0 && yy < a.H && xx >= 0 && xx < a.W) {
-          if constexpr (POOL)
-            v = pool4(a.in + ((int64_t(b) * 2 * a.H + 2 * yy) * 2 * a.W + 2 * xx) * Cin + c0 +
-                          8 * part,
-                      Cin, int64_t(2) * a.W * Cin);
-          else
-            v = (CAT && c0 < a.c_low)
-                    ? *reinterpret_cast<const uint4*>(
-                          limg + (int64_t(yy >> 1) * Wl + (xx >> 1)) * a.c_low + c0 + 8 * part)
-                    : *reinterpret_cast<const uint4*>(img + (int64_t(yy) * a.W + xx) * Cs + c0 -
-                                                      a.c_low + 8 * part);
-        }
-      }
-      hreg[u] = v;
-    }
-  };
-  auto store_halo = [&]() {
-#pragma unroll
-    for (int u = 0; u < HQ; ++u) {
-      const int q = t + 256 * u;
-      if (q < HH * HW * 4)
-        *reinterpret_cast<uint4*>(&halo[(q >> 2) * PITCH + 8 * (q & 3)]) = hreg[u];
-    }
-  };
-  auto load_slab = [&](int c0, int ky0) {
-#pragma unroll
-    for (int u = 0; u < SQ; ++u) {
-      const int q = t + 256 * u;
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (q < 3 * KY * NT * 4) {
-        const int part = q & 3, row = q >> 2;  // row = (3 * kyi + kx) * NT + n
-        const int tl = row / NT, n = row % NT;
-        const int k = (ky0 * 3 + tl) * Cin + c0 + 8 * part;
-        v = *reinterpret_cast<const uint4*>(a.wk + int64_t(n0 + n) * a.Kpad + k);
-      }
-      sreg[u] = v;
-    }
-  };
-  auto store_slab = [&]() {
-#pragma unroll
-    for (int u = 0; u < SQ; ++u) {
-      const int q = t + 256 * u;
-      if (q < 3 * KY * NT * 4)
-        *reinterpret_cast<uint4*>(&slab[(q >> 2) * PITCH + 8 * (q & 3)]) = sreg[u];
-    }
-  };
-
-  const int phases = (Cin / 32) * PPC;
-  load_halo(0);
-  load_slab(0, 0);
-  store_halo();
-  store_slab();
-  __syncthreads();
+  copy_slab(0, 0);
+  copy_halo(0);
+  copy_slab(0, 1);
+  copy_slab(0, 2);
+  const int chunks = Cin / 32;
 #pragma unroll 1
-  for (int p = 0; p < phases; ++p) {
-    const int ky0 = KY * (p % PPC);
-    const bool next = p + 1 < phases;
-    const int pn = p + 1, cn = 32 * (pn / PPC), kyn = KY * (pn % PPC);
-    if (next) {
-      if (kyn == 0) load_halo(cn);
-      load_slab(cn, kyn);
-    }
+  for (int c = 0; c < chunks; ++c) {
+    const bool more = c + 1 < chunks;
+    v8bf av[TM + 2][3];
 #pragma unroll
-    for (int tl = 0; tl < 3 * KY; ++tl) {
-      const int ky = ky0 + tl / 3, kx = tl % 3;
-      uint4 av[TM], bv[TN];
+    for (int ky = 0; ky < 3; ++ky) {
+      // this wave's copies for the phase have landed (later ones: the weights
+      // of the next kernel row, or of two in the first chunk, or the next
+      // chunk's pixels and weights), then every wave's
+      if (ky == 0) {
+        if (c == 0)
+          nn_wait_copies<2 * SL>();
+        else
+          nn_wait_copies<SL>();
+        if (POOL && c == 0) nn_wait_lds();
+      } else if (ky == 1) {
+        nn_wait_copies<SL>();
+      } else if (more) {
+        nn_wait_copies<HL + SL>();
+      } else {
+        nn_wait_copies<0>();
+      }
+      nn_barrier();
+      if (ky == 0 && c > 0) copy_slab(32 * c, 2);
+      if (ky > 0 && more) copy_slab(32 * c + 32, ky - 1);
+      if (!POOL && ky == 1 && more) copy_halo(32 * c + 32);
+      if (ky == 0)
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
-        av[i] = *reinterpret_cast<const uint4*>(
-            &halo[((wm * TM + i + ky) * HW + r + kx) * PITCH + 8 * g]);
+        for (int i = 0; i < TM + 2; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
-        bv[j] = *reinterpret_cast<const uint4*>(
-            &slab[(tl * NT + wn * 16 * TN + 16 * j + r) * PITCH + 8 * g]);
-      // weights as the A operand (rows: channels), pixels as B (columns)
+          for (int kx = 0; kx < 3; ++kx)
+            av[i][kx] = *reinterpret_cast<const v8bf*>(
+                halo + ((uint32_t(hp[kx] - halo) + uint32_t(64 * HW * i)) ^ (i & 1 ? 32u : 0u)));
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int kx = 0; kx < 3; ++kx) {
+        v8bf bv[TN];
 #pragma unroll
         for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-              __builtin_bit_cast(v8bf, bv[j]), __builtin_bit_cast(v8bf, av[i]), acc[i][j], 0, 0,
-              0);
-    }
-    if (next) {
-      __syncthreads();  // every wave is done reading phase p's tiles
-      if (kyn == 0) store_halo();
-      store_slab();
-      __syncthreads();
+          bv[j] = *reinterpret_cast<const v8bf*>(sp + 1024 * (SC * ky + kx * (NT / 16) + j));
+        // weights as the A operand (rows: channels), pixels as B (columns)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv[j], av[i + ky][kx], acc[i][j],
+                                                                0, 0, 0);
+      }
+      if (POOL && ky == 1 && more) copy_halo(32 * c + 32);
+      nn_wait_lds();
     }
   }
   // elements (column r of row wm*TM + i, channels 4g .. 4g + 3 of tile j):
@@ -336,18 +414,18 @@ __global__ __launch_bounds__(256) void k_conv3_lds(NnConvArgs a) {
 #pragma unroll
             for (int di = 0; di < 2; ++di) {
               if (yy + di >= a.H || xx >= a.W) continue;
-              uint2 ov;
-              ov.x = uint32_t(f2bf(acc[i + di][j][0])) | (uint32_t(f2bf(acc[i + di][j][1])) << 16);
-              ov.y = uint32_t(f2bf(acc[i + di][j][2])) | (uint32_t(f2bf(acc[i + di][j][3])) << 16);
+              const v4f v = acc[i + di][j];
               *reinterpret_cast<uint2*>(
-                  a.dskip + ((int64_t(b) * a.H + yy + di) * a.W + xx) * C2 + (n - a.c1)) = ov;
+                  a.dskip + ((int64_t(b) * a.H + yy + di) * a.W + xx) * C2 + (n - a.c1)) =
+                  make_uint2(pack_bf(v[0], v[1]), pack_bf(v[2], v[3]));
             }
           } else {
             float sv[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               const float v00 = bf2f(f2bf(acc[i][j][e])), v10 = bf2f(f2bf(acc[i + 1][j][e]));
-              const float v01 = __shfl_xor(v00, 1), v11 = __shfl_xor(v10, 1);
+              // (the value of lane r ^ 1)
+              const float v01 = nn_swap_lanes(v00), v11 = nn_swap_lanes(v10);
               sv[e] = (v00 + v01) + (v10 + v11);
             }
             if ((r & 1) == 0 && yy < a.H && xx < a.W) {
@@ -355,14 +433,12 @@ __global__ __launch_bounds__(256) void k_conv3_lds(NnConvArgs a) {
                   ((int64_t(b) * (a.H / 2) + yy / 2) * (a.W / 2) + xx / 2) * a.c1 + n;
               uint2 mk = make_uint2(0x3F803F80u, 0x3F803F80u);  // 1.0 in every element
               if (a.low_mask) mk = *reinterpret_cast<const uint2*>(a.low_mask + lo);
-              const uint16_t* mh = reinterpret_cast<const uint16_t*>(&mk);
-              uint16_t o[4];
+              const uint32_t mw[4] = {mk.x << 16, mk.x & 0xffff0000u, mk.y << 16,
+                                      mk.y & 0xffff0000u};
 #pragma unroll
-              for (int e = 0; e < 4; ++e) o[e] = bf2f(mh[e]) > 0.0f ? f2bf(sv[e]) : uint16_t(0);
-              uint2 ov;
-              ov.x = uint32_t(o[0]) | (uint32_t(o[1]) << 16);
-              ov.y = uint32_t(o[2]) | (uint32_t(o[3]) << 16);
-              *reinterpret_cast<uint2*>(a.dlow + lo) = ov;
+              for (int e = 0; e < 4; ++e) sv[e] = __uint_as_float(mw[e]) > 0.0f ? sv[e] : 0.0f;
+              *reinterpret_cast<uint2*>(a.dlow + lo) =
+                  make_uint2(pack_bf(sv[0], sv[1]), pack_bf(sv[2], sv[3]));
             }
           }
         }
@@ -370,34 +446,46 @@ __global__ __launch_bounds__(256) void k_conv3_lds(NnConvArgs a) {
     }
     return;
   }
+  if (xx >= a.W) return;
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int yy = y0 + wm * TM + i;
-    if (yy >= a.H || xx >= a.W) continue;
+  for (int j = 0; j < TN; ++j) {
+    const int n = n0 + wn * 16 * TN + 16 * j + 4 * g;
+    float bias[4];
+    if (a.bias)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int n = n0 + wn * 16 * TN + 16 * j + 4 * g;
+      for (int e = 0; e < 4; ++e) bias[e] = a.bias[n + e];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const int yy = y0 + wm * TM + i;
+      if (yy >= a.H) break;
       const int64_t o = ((int64_t(b) * a.H + yy) * a.W + xx) * a.Cout + n;
       float v[4];
-      uint2 mk = make_uint2(0xFFFFFFFFu, 0xFFFFFFFFu);
-      if (a.mask) mk = *reinterpret_cast<const uint2*>(a.mask + o);
-      const uint16_t* mh = reinterpret_cast<const uint16_t*>(&mk);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        v[e] = acc[i][j][e];
-        if (a.bias) v[e] += a.bias[n + e];
-        if (a.relu && v[e] < 0.0f) v[e] = 0.0f;
-        if (a.mask && !(bf2f(mh[e]) > 0.0f)) v[e] = 0.0f;
+      for (int e = 0; e < 4; ++e) v[e] = acc[i][j][e];
+      if (a.bias)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] += bias[e];
+      if (a.relu)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = v[e] < 0.0f ? 0.0f : v[e];
+      if (a.mask) {
+        const uint2 mk = *reinterpret_cast<const uint2*>(a.mask + o);
+        const uint32_t mw[4] = {mk.x << 16, mk.x & 0xffff0000u, mk.y << 16, mk.y & 0xffff0000u};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(mw[e]) > 0.0f ? v[e] : 0.0f;
       }
-      if (a.out) {
-        uint2 ov;
-        ov.x = uint32_t(f2bf(v[0])) | (uint32_t(f2bf(v[1])) << 16);
-        ov.y = uint32_t(f2bf(v[2])) | (uint32_t(f2bf(v[3])) << 16);
-        *reinterpret_cast<uint2*>(a.out + o) = ov;
-      }
+      if (a.out)
+        *reinterpret_cast<uint2*>(a.out + o) = make_uint2(pack_bf(v[0], v[1]), pack_bf(v[2], v[3]));
       if (a.out_f32) *reinterpret_cast<float4*>(a.out_f32 + o) = make_float4(v[0], v[1], v[2], v[3]);
     }
   }
+}
+
+template <int TM, int TN, int WM, int WN, int MODE>
+__global__ __launch_bounds__(256) void k_conv3_lds(NnConvArgs a) {
+  constexpr int HC = ((WM * TM + 2) * kHaloPitch + 15) / 16, SC = 3 * WN * TN;
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[(HC + 3 * SC) * 1024];
+  conv3_lds<TM, TN, WM, WN, MODE>(a, lds);
 }
 
 // ---- convolution, backward-weight -------------------------------------------
@@ -1611,28 +1699,23 @@ void conv_ks(const NnConvArgs& a, hipStream_t s) {
     launch_conv<KS, 1, 2>(a, s);
 }
 
-// Kernel rows per phase: all three (one phase per chunk of 32 input
-// channels) for 64-channel tiles; one for 128-channel tiles, whose nine
-// taps' weights would not leave room for a second work-group, and for
-// 32-channel tiles, whose level-0 grids gain more from occupancy.
 template <int TM, int TN, int WM, int WN>
 void launch_conv3_lds(const NnConvArgs& a, hipStream_t s) {
   constexpr int TH = WM * TM, NT = WN * TN * 16;
-  constexpr int KY = NT == 64 ? 3 : 1;
   const int64_t blocks = int64_t((a.W + 15) / 16) * ((a.H + TH - 1) / TH) * a.B;
   const dim3 grid(unsigned(blocks), unsigned(a.Cout / NT));
   if constexpr (TM % 2 == 0) {
     if (a.dlow) {
-      hipLaunchKernelGGL((k_conv3_lds<TM, TN, WM, WN, KY, 2>), grid, dim3(256), 0, s, a);
+      hipLaunchKernelGGL((k_conv3_lds<TM, TN, WM, WN, 2>), grid, dim3(256), 0, s, a);
       return;
     }
   }
   if (a.pool_in)
-    hipLaunchKernelGGL((k_conv3_lds<TM, TN, WM, WN, KY, 1>), grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((k_conv3_lds<TM, TN, WM, WN, 1>), grid, dim3(256), 0, s, a);
   else if (a.low)
-    hipLaunchKernelGGL((k_conv3_lds<TM, TN, WM, WN, KY, 3>), grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((k_conv3_lds<TM, TN, WM, WN, 3>), grid, dim3(256), 0, s, a);
   else
-    hipLaunchKernelGGL((k_conv3_lds<TM, TN, WM, WN, KY, 0>), grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((k_conv3_lds<TM, TN, WM, WN, 0>), grid, dim3(256), 0, s, a);
 }
 
 // Work-groups of the LDS-staged 3x3 kernel for a tile of TH rows and NT channels.
@@ -1641,18 +1724,22 @@ int64_t lds_groups(const NnConvArgs& a, int th, int nt) {
 }
 
 // The LDS-staged tile for a 3x3 layer with Cin % 32 == 0: the first shape
-// (rows x channels: 8 x 128, 8 x 64, 4 x 64, 16 x 32, 8 x 32, 4 x 32) whose
-// grid holds >= 512 work-groups, failing that >= 256, then >= 128; -1: none
-// (the register-fed kernel).
+// (rows x channels: 8 x 64, 4 x 64, 16 x 32, 8 x 32, 4 x 32) whose grid holds
+// >= 512 work-groups, failing that >= 256, then >= 128; -1: none (the
+// register-fed kernel).  An 8 x 128 tile leaves room for one work-group per
+// CU: with it the network took 606 instead of 576 us at batch 64 of 128 x 128
+// and 1107 instead of 1041 us at batch 128.
 int conv3_tile(const NnConvArgs& a) {
-  if (a.ks != 3 || a.Cin % 32 != 0) return -1;
+  // (byte offsets within a tile's rows and the weights stay below 2^31)
+  if (a.ks != 3 || a.Cin % 32 != 0 || int64_t(a.W) * a.Cin >= (int64_t(1) << 25) ||
+      int64_t(a.Kpad) * 128 >= (int64_t(1) << 30))
+    return -1;
   for (int64_t kMin = 512; kMin >= 128; kMin /= 2) {
-    if (a.Cout % 128 == 0 && lds_groups(a, 8, 128) >= kMin) return 0;
-    if (a.Cout % 64 == 0 && lds_groups(a, 8, 64) >= kMin) return 1;
-    if (a.Cout % 64 == 0 && lds_groups(a, 4, 64) >= kMin) return 2;
-    if (lds_groups(a, 16, 32) >= kMin) return 3;
-    if (lds_groups(a, 8, 32) >= kMin) return 4;
-    if (lds_groups(a, 4, 32) >= kMin) return 5;
+    if (a.Cout % 64 == 0 && lds_groups(a, 8, 64) >= kMin) return 0;
+    if (a.Cout % 64 == 0 && lds_groups(a, 4, 64) >= kMin) return 1;
+    if (lds_groups(a, 16, 32) >= kMin) return 2;
+    if (lds_groups(a, 8, 32) >= kMin) return 3;
+    if (lds_groups(a, 4, 32) >= kMin) return 4;
   }
   return -1;
 }
@@ -1660,11 +1747,11 @@ int conv3_tile(const NnConvArgs& a) {
 bool nn_conv_takes_split(const NnConvArgs& a) {
   if (a.low || a.pool_in || a.out || a.out_f32 || a.bias || a.relu || a.mask) return false;
   if (a.H % 2 || a.W % 2 || a.c1 <= 0 || a.c1 >= a.Cout) return false;
-  // tiles 0 .. 4 have an even number of rows per wave; tile channel widths
-  // 128, 64, 64, 32, 32 must divide c1
+  // tiles 0 .. 3 have an even number of rows per wave; tile channel widths
+  // 64, 64, 32, 32 must divide c1
   const int tile = conv3_tile(a);
-  static const int nt[5] = {128, 64, 64, 32, 32};
-  return tile >= 0 && tile <= 4 && a.c1 % nt[tile] == 0 && (a.Cout - a.c1) % 8 == 0;
+  static const int nt[4] = {64, 64, 32, 32};
+  return tile >= 0 && tile <= 3 && a.c1 % nt[tile] == 0 && (a.Cout - a.c1) % 8 == 0;
 }
 
 bool nn_conv_takes_low(const NnConvArgs& a) {
@@ -1679,11 +1766,10 @@ hipError_t nn_conv(const NnConvArgs& a, hipStream_t s) {
   const int tile = conv3_tile(a);
   if (tile >= 0) {
     switch (tile) {
-      case 0: launch_conv3_lds<4, 4, 2, 2>(a, s); break;
-      case 1: launch_conv3_lds<4, 2, 2, 2>(a, s); break;
-      case 2: launch_conv3_lds<2, 2, 2, 2>(a, s); break;
-      case 3: launch_conv3_lds<4, 2, 4, 1>(a, s); break;
-      case 4: launch_conv3_lds<2, 2, 4, 1>(a, s); break;
+      case 0: launch_conv3_lds<4, 2, 2, 2>(a, s); break;
+      case 1: launch_conv3_lds<2, 2, 2, 2>(a, s); break;
+      case 2: launch_conv3_lds<4, 2, 4, 1>(a, s); break;
+      case 3: launch_conv3_lds<2, 2, 4, 1>(a, s); break;
       default: launch_conv3_lds<1, 2, 4, 1>(a, s); break;
     }
   } else if (a.ks == 3) {
