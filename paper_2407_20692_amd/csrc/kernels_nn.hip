@@ -202,16 +202,24 @@ __global__ __launch_bounds__(256) void k_conv(NnConvArgs a) {
 // and each pixel fragment read once per tap.
 constexpr int kHaloPitch = 20;
 
-typedef __attribute__((address_space(3))) uint8_t* nn_lds_t;
+typedef int nn_i4 __attribute__((ext_vector_type(4)));
 
 // LDS-direct copy of 16 bytes per lane to 1 KB from dst; an offset at or above
-// 2^31 delivers zeros
-__device__ __forceinline__ void copy_lds16(__amdgpu_buffer_rsrc_t from, uint8_t* dst,
-                                           uint32_t voff, uint32_t soff) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(from, (nn_lds_t)dst, 16, int(voff), int(soff), 0, 0);
+// 2^31 delivers zeros.  (Assembly: for the builtin the compiler waits for all
+// copies before transposing reads of the same array.  Nothing else in these
+// kernels uses M0.)
+__device__ __forceinline__ void copy_lds16(nn_i4 from, uint8_t* dst, uint32_t voff,
+                                           uint32_t soff) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n"
+      "s_nop 4\n"
+      "buffer_load_dwordx4 %1, %2, %3 offen lds\n" ::"s"(uint32_t(reinterpret_cast<uintptr_t>(dst))),
+      "v"(voff), "s"(from), "s"(soff)
+      : "memory");
 }
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* p) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, 0x7fffffff, 0x00020000);
+__device__ __forceinline__ nn_i4 buffer_at(const void* p) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  return nn_i4{int(uint32_t(a)), int(uint32_t(a >> 32) & 0xffffu), 0x7fffffff, 0x00020000};
 }
 
 // waits until at most n of this wave's copies are in flight
@@ -653,32 +661,47 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(NnWgradArgs a) {
 // c + 4 q .. + 3, and lane j receives channel c + j at pixels p .. p + 3).
 // K slots 8 g .. 8 g + 7 of a 32-pixel step hold pixels 4 g .. 4 g + 3 and
 // 16 + 4 g .. + 3, so the eight pixels that half a wave reads in one go are
-// consecutive; with row pitches of an odd multiple of 32 bytes they cover all
-// 64 LDS banks once.  Wave w takes input channels 16 (w & 1) + [0, 16); for
+// consecutive.  Wave w takes input channels 16 (w & 1) + [0, 16); for
 // NT = 64 it takes output channels 32 (w >> 1) + [0, 32) and every step, for
 // NT = 32 all 32 channels and the steps of parity w >> 1.  A wave's 18 tiles
 // (2 channel tiles x 9 taps) go to the pixel split's slot of the partial
 // buffer (added to dW with FP32 atomics when there is none); the bias
 // gradient is summed from the dY operands of the waves on input channels
 // 0 .. 15 of the first slice.
+//
+// With one work-group per CU and two to eight blocks each, what bounds it is
+// the latency of a block.  Blocks go from memory to LDS directly, pixels
+// outside the image as out-of-range lanes, which deliver zeros, into three
+// stages: two blocks are in flight while one is multiplied, behind one
+// barrier per block.  (A pooled input goes through registers, one block
+// ahead.)  Rows of the stages are as long as their data; 32-byte groups of a
+// row are exchanged by its pixel number so that eight consecutive pixels
+// cover all 64 LDS banks once: of 64-byte rows by bit 2, of 128-byte rows by
+// bits 1 and 2.  Launches of a training step of batch 16 at 128 x 128 (their
+// start of about 4 us included): 32 channels at 128 x 128 27 -> 19 us, 64 at
+// 64 x 64 21 -> 17 us, 128 at 32 x 32 18 -> 16 us, against staging through
+// registers with 64-bit addresses and a branch per piece, one block ahead.
 template <int NT, int TW, int R>
-__global__ __launch_bounds__(256) void k_conv3_wgrad(NnWgradArgs a) {
+constexpr int wgrad_stage() {   // bytes
+  return (((R + 2) * (TW + 2) + 15) / 16 + TW * R * NT / 512) * 1024;
+}
+
+template <int NT, int TW, int R, bool POOL>
+__device__ __forceinline__ void conv3_wgrad(const NnWgradArgs& a, uint8_t* lds) {
   constexpr int PXB = TW * R;             // pixels per block
   constexpr int STEPS = PXB / 32;         // 32-pixel matrix-core steps per block
-  constexpr int PY = NT + 16;             // dY row pitch (elements): 96 or 160 bytes
-  constexpr int PX = 48;                  // halo row pitch (elements): 96 bytes
   constexpr int HW = TW + 2, HP = (R + 2) * HW;
-  static_assert(PXB % 64 == 0 && TW % 16 == 0, "block shape");
+  constexpr int XC = (HP + 15) / 16, YC = PXB * NT / 512;   // 1 KB copies per block
+  constexpr int XU = (XC + 3) / 4, YU = YC / 4;             // per wave at most
+  constexpr int CL = (POOL ? 0 : XC / 4) + YU;              // per wave at least
+  constexpr int STAGE = wgrad_stage<NT, TW, R>(), RP = 36;
+  static_assert(PXB % 64 == 0 && TW % 16 == 0 && R % 2 == 0 && YC % 4 == 0, "block shape");
   static_assert(NT == 32 || NT == 64, "channel tile");
-  // the dY block, then the halo; reused at the end (NT = 32) to combine the
-  // two step parities: [9][32][RP] floats of dW, then 32 floats of db
-  constexpr int TY = PXB * PY, TX = HP * PX, RP = 36;
-  static_assert(NT == 64 || (9 * 32 * RP + 32) * 4 <= (TY + TX) * 2, "reduction space");
-  __shared__ __attribute__((aligned(16))) uint16_t lds[TY + TX];
-  uint16_t* const ty = lds;
-  uint16_t* const tx = lds + TY;
+  // reused at the end (NT = 32) to combine the two step parities: [9][32][RP]
+  // floats of dW, then 32 floats of db
+  static_assert(NT == 64 || (9 * 32 * RP + 32) * 4 <= 3 * STAGE, "reduction space");
   const int t = threadIdx.x;
-  const int lane = t & 63, wave = t >> 6;
+  const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int r = lane & 15, g = lane >> 4;
   const int ct = wave & 1;
   const int nt0 = NT == 64 ? 2 * (wave >> 1) : 0;
@@ -697,78 +720,128 @@ __global__ __launch_bounds__(256) void k_conv3_wgrad(NnWgradArgs a) {
   for (int u = 0; u < 9; ++u) acc[u][0] = acc[u][1] = v4f{0, 0, 0, 0};
   float bsum[2] = {0.0f, 0.0f};
 
-  // staging: dY piece c = (pixel c / (NT / 8), channels 8 (c % (NT / 8)));
-  // halo piece c = (halo pixel c / 4, channels 8 (c % 4))
-  constexpr int YQ = PXB * NT / 8 / 256;
-  constexpr int XQ = (HP * 4 + 255) / 256;
-  static_assert(YQ * 256 == PXB * NT / 8, "dY pieces");
-  uint4 yv[YQ], xv[XQ];
-  auto load = [&](int64_t blk) {
-    const int ix = int(blk % bx);
-    const int64_t rest = blk / bx;
-    const int iy = int(rest % by);
-    const int64_t b = rest / by;
-    const int x0 = ix * TW, y0 = iy * R;
+  // Copies: the halo's 16 pixels x 64 bytes each, then dY's 1 KB of pixels;
+  // wave w takes copies w, w + 4, ... of either; offsets are from the block's
+  // first halo pixel (or the half-resolution one that it reads) and first pixel
+  const bool low = !POOL && c0 < a.c_low;
+  const int Xc = low ? a.c_low : Cin - a.c_low, Xw = low ? a.W / 2 : a.W;
+  const int xpiece = (lane & 3) ^ ((lane >> 4 & 1) << 1);
+  uint32_t xoff[XU], xpos[XU], yoff[YU];
 #pragma unroll
-    for (int u = 0; u < YQ; ++u) {
-      const int c = t + 256 * u;
-      const int px = c / (NT / 8), part = c % (NT / 8);
-      const int y = y0 + px / TW, x = x0 + px % TW;
-      yv[u] = make_uint4(0, 0, 0, 0);
-      if (y < a.H && x < a.W)
-        yv[u] = *reinterpret_cast<const uint4*>(a.dy + ((b * a.H + y) * a.W + x) * a.Cout + n0 +
-                                                8 * part);
+  for (int u = 0; u < XU; ++u) {
+    const int px = 16 * (wave + 4 * u) + (lane >> 2);
+    const int hy = px / HW, hx = px - hy * HW;
+    const int oy = low ? (hy + 1) >> 1 : hy, ox = low ? (hx + 1) >> 1 : hx;
+    xoff[u] = uint32_t((oy * Xw + ox) * Xc + 8 * xpiece) * 2;
+    xpos[u] = px < HP ? uint32_t(hy) << 16 | uint32_t(hx) : 0x7fff0000u;
+  }
+  constexpr int YL = NT / 8;   // lanes per dY pixel
+  const int ypiece = NT == 64 ? (lane & 7) ^ ((lane >> 4 & 3) << 1) : xpiece;
+  const int yx = lane / YL;    // its column in the copy
+#pragma unroll
+  for (int u = 0; u < YU; ++u) {
+    const int px = 64 / YL * (wave + 4 * u);
+    yoff[u] = uint32_t(((px / TW) * a.W + px % TW + yx) * a.Cout + 8 * ypiece) * 2;
+  }
+  struct Block {
+    int64_t b;
+    int x0, y0;
+  };
+  auto block = [&](int64_t blk) {
+    const uint32_t i = uint32_t(blk), q = i / uint32_t(bx);
+    return Block{int64_t(q / uint32_t(by)), int(i % uint32_t(bx)) * TW, int(q % uint32_t(by)) * R};
+  };
+  auto copy = [&](const Block& k, int stage) {
+    uint8_t* dst = lds + stage * STAGE;
+    if constexpr (!POOL) {
+      const auto rx =
+          low ? buffer_at(a.low + ((k.b * (a.H / 2) + k.y0 / 2 - 1) * Xw + k.x0 / 2 - 1) * Xc + c0)
+              : buffer_at(a.in + ((k.b * a.H + k.y0 - 1) * Xw + k.x0 - 1) * Xc + c0 - a.c_low);
+#pragma unroll
+      for (int u = 0; u < XU; ++u)
+        if (XC % 4 == 0 || u + 1 < XU || wave < XC % 4) {
+          const uint32_t y = uint32_t(k.y0 - 1) + (xpos[u] >> 16);
+          const uint32_t x = uint32_t(k.x0 - 1) + (xpos[u] & 0xffffu);
+          copy_lds16(rx, dst + (wave + 4 * u) * 1024,
+                     y < uint32_t(a.H) && x < uint32_t(a.W) ? xoff[u] : 0x80000000u, 0);
+        }
     }
+    const auto ry = buffer_at(a.dy + ((k.b * a.H + k.y0) * a.W + k.x0) * a.Cout + n0);
 #pragma unroll
-    for (int u = 0; u < XQ; ++u) {
+    for (int u = 0; u < YU; ++u) {
+      const int px = 64 / YL * (wave + 4 * u);
+      const bool in = k.y0 + px / TW < a.H && k.x0 + px % TW + yx < a.W;
+      copy_lds16(ry, dst + (XC + wave + 4 * u) * 1024, in ? yoff[u] : 0x80000000u, 0);
+    }
+  };
+  // the pooled halo, by registers
+  constexpr int PU = POOL ? (HP * 4 + 255) / 256 : 1;
+  uint4 xv[PU];
+  auto pool_load = [&](const Block& k) {
+#pragma unroll
+    for (int u = 0; u < PU; ++u) {
       const int c = t + 256 * u;
-      const int hp = c >> 2, part = c & 3;
-      const int y = y0 + hp / HW - 1, x = x0 + hp % HW - 1;
+      const int y = k.y0 + (c >> 2) / HW - 1, x = k.x0 + (c >> 2) % HW - 1;
       xv[u] = make_uint4(0, 0, 0, 0);
-      if (c < HP * 4 && y >= 0 && y < a.H && x >= 0 && x < a.W && a.pool_in)
-        xv[u] = pool4(a.in + ((b * 2 * a.H + 2 * y) * 2 * a.W + 2 * x) * Cin + c0 + 8 * part, Cin,
-                      int64_t(2) * a.W * Cin);
-      else if (c < HP * 4 && y >= 0 && y < a.H && x >= 0 && x < a.W)
-        xv[u] = c0 < a.c_low
-                    ? *reinterpret_cast<const uint4*>(
-                          a.low + ((b * (a.H / 2) + (y >> 1)) * (a.W / 2) + (x >> 1)) * a.c_low +
-                          c0 + 8 * part)
-                    : *reinterpret_cast<const uint4*>(
-                          a.in + ((b * a.H + y) * a.W + x) * (Cin - a.c_low) + c0 - a.c_low +
-                          8 * part);
+      if (c < HP * 4 && y >= 0 && y < a.H && x >= 0 && x < a.W)
+        xv[u] = pool4(a.in + ((k.b * 2 * a.H + 2 * y) * 2 * a.W + 2 * x) * Cin + c0 + 8 * (c & 3),
+                      Cin, int64_t(2) * a.W * Cin);
     }
   };
-  auto store = [&]() {
+  auto pool_store = [&](int stage) {
 #pragma unroll
-    for (int u = 0; u < YQ; ++u) {
-      const int c = t + 256 * u;
-      *reinterpret_cast<uint4*>(&ty[(c / (NT / 8)) * PY + 8 * (c % (NT / 8))]) = yv[u];
-    }
-#pragma unroll
-    for (int u = 0; u < XQ; ++u) {
-      const int c = t + 256 * u;
-      if (c < HP * 4) *reinterpret_cast<uint4*>(&tx[(c >> 2) * PX + 8 * (c & 3)]) = xv[u];
+    for (int u = 0; u < PU; ++u) {
+      const int c = t + 256 * u, px = c >> 2;
+      if (c < HP * 4)
+        *reinterpret_cast<uint4*>(lds + stage * STAGE + 64 * px +
+                                  16 * ((c & 3) ^ ((px >> 2 & 1) << 1))) = xv[u];
     }
   };
+
   typedef short v4s __attribute__((ext_vector_type(4)));
   typedef short v8s __attribute__((ext_vector_type(8)));
   typedef __attribute__((address_space(3))) v4s lds_v4s;
-  // lane parts of the addresses: pixel 4 g + (r >> 2), channels 4 (r & 3)
-  const uint16_t* ybase = ty + (4 * g + (r >> 2)) * PY + 16 * nt0 + 4 * (r & 3);
-  const uint16_t* xbase = tx + (4 * g + (r >> 2)) * PX + 16 * ct + 4 * (r & 3);
-  auto pair = [](const uint16_t* lo, const uint16_t* hi) {
+  // lane parts of the addresses: pixel 4 g + (r >> 2), channels 4 (r & 3); of the
+  // halo for pixel numbers 0 .. 7 modulo 8 further on
+  const int lp = 4 * g + (r >> 2);
+  uint32_t xb[8], yb[2];
+#pragma unroll
+  for (int c = 0; c < 8; ++c)
+    xb[c] = uint32_t(64 * (lp + c) + 32 * (ct ^ ((lp + c) >> 2 & 1)) + 8 * (r & 3));
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    yb[i] = uint32_t(XC * 1024 + 2 * NT * lp +
+                     32 * ((nt0 + i) ^ (NT == 64 ? lp >> 1 & 3 : lp >> 2 & 1)) + 8 * (r & 3));
+  auto pair = [](const uint8_t* lo, const uint8_t* hi) {
     const v4s u = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)lo);
     const v4s v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)hi);
     const v8s w = {u[0], u[1], u[2], u[3], v[0], v[1], v[2], v[3]};
     return __builtin_bit_cast(v8bf, w);
   };
 
-  if (blo < bhi) load(blo);
+  if (blo < bhi) {
+    copy(block(blo), 0);
+    if constexpr (POOL) {
+      pool_load(block(blo));
+      pool_store(0);
+      nn_wait_lds();
+    }
+    if (blo + 1 < bhi) copy(block(blo + 1), 1);
+  }
+  int stage = 0;
 #pragma unroll 1
   for (int64_t blk = blo; blk < bhi; ++blk) {
-    store();
-    __syncthreads();
-    if (blk + 1 < bhi) load(blk + 1);
+    // this wave's copies of the block have landed (the next block's may be in
+    // flight), then every wave's, and every wave has read the last block
+    if (blk + 1 < bhi)
+      nn_wait_copies<CL>();
+    else
+      nn_wait_copies<0>();
+    nn_barrier();
+    const int s1 = stage == 2 ? 0 : stage + 1, s2 = stage == 0 ? 2 : stage - 1;
+    if (blk + 2 < bhi) copy(block(blk + 2), s2);
+    if (POOL && blk + 1 < bhi) pool_load(block(blk + 1));
+    const uint8_t* base = lds + stage * STAGE;
 #pragma unroll
     for (int s = 0; s < STEPS; ++s) {
       if (NT == 32 && (s & 1) != par) continue;
@@ -778,7 +851,7 @@ __global__ __launch_bounds__(256) void k_conv3_wgrad(NnWgradArgs a) {
       v8bf av[2];
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        av[i] = pair(ybase + p0 * PY + 16 * i, ybase + p1 * PY + 16 * i);
+        av[i] = pair(base + yb[i] + p0 * 2 * NT, base + yb[i] + p1 * 2 * NT);
         if (bias) {
           const v8s e = __builtin_bit_cast(v8s, av[i]);
 #pragma unroll
@@ -790,16 +863,19 @@ __global__ __launch_bounds__(256) void k_conv3_wgrad(NnWgradArgs a) {
       for (int ky = 0; ky < 3; ++ky)
 #pragma unroll
         for (int kx = 0; kx < 3; ++kx) {
-          const int o = ky * HW + kx;
-          const v8bf bv = pair(xbase + (h0 + o) * PX, xbase + (h1 + o) * PX);
+          const int u0 = h0 + ky * HW + kx, u1 = h1 + ky * HW + kx;
+          const v8bf bv = pair(base + xb[u0 & 7] + 64 * (u0 & ~7), base + xb[u1 & 7] + 64 * (u1 & ~7));
 #pragma unroll
           for (int i = 0; i < 2; ++i)
             acc[3 * ky + kx][i] =
                 __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], bv, acc[3 * ky + kx][i], 0, 0, 0);
         }
     }
-    __syncthreads();
+    if (POOL && blk + 1 < bhi) pool_store(s1);
+    nn_wait_lds();
+    stage = s1;
   }
+  __syncthreads();
   // element (n = n0 + 16 (nt0 + i) + 4 g + e, ci = c0 + 16 ct + r) of tap u
   float* pz = a.part ? a.part + int64_t(blockIdx.z) * (int64_t(a.Cout) * K + a.Cout) : nullptr;
   float bv[2];
@@ -824,8 +900,7 @@ __global__ __launch_bounds__(256) void k_conv3_wgrad(NnWgradArgs a) {
             atomicAdd(&a.dw[o], acc[u][i][e]);
         }
   } else {
-    // the waves of parity 1 add their tiles to those of parity 0 in LDS (the
-    // loop's last barrier has freed it), then the work-group stores the
+    // the waves of parity 1 add their tiles to those of parity 0 in LDS, then the work-group stores the
     // 32 x 9 x 32 tile with coalesced writes
     float* red = reinterpret_cast<float*>(lds);
     float* rb = red + 9 * 32 * RP;
@@ -872,6 +947,12 @@ __global__ __launch_bounds__(256) void k_conv3_wgrad(NnWgradArgs a) {
         atomicAdd(&a.db[n], bv[i]);
     }
   }
+}
+
+template <int NT, int TW, int R, bool POOL>
+__global__ __launch_bounds__(256) void k_conv3_wgrad(NnWgradArgs a) {
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[3 * wgrad_stage<NT, TW, R>()];
+  conv3_wgrad<NT, TW, R, POOL>(a, lds);
 }
 
 // dw[i] += sum over splits z of part[z][i] (i < nw), db[i - nw] += the same
@@ -1782,6 +1863,14 @@ hipError_t nn_conv(const NnConvArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int NT, int TW, int R>
+void launch_conv3_wgrad(const NnWgradArgs& a, dim3 grid, hipStream_t s) {
+  if (a.pool_in)
+    hipLaunchKernelGGL((k_conv3_wgrad<NT, TW, R, true>), grid, dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL((k_conv3_wgrad<NT, TW, R, false>), grid, dim3(256), 0, s, a);
+}
+
 // Launch shape of a weight gradient: the kernel (3x3 all-taps kernel with
 // NT = 64 or 32 and block width TW = 64, 32 or 16; else the general kernel
 // for ks = 3 or 1 with NT = 64 or 32) and the grid, whose z dimension splits
@@ -1797,7 +1886,10 @@ WgradPlan wgrad_plan(const NnWgradArgs& a) {
   const int NT = wide ? 64 : 32;
   p.gx = unsigned(a.Cout / NT);
   int64_t z;
-  if (a.ks == 3 && a.Cin % 32 == 0) {
+  // (32-bit block numbers, and byte offsets within a block's rows below 2^31)
+  const int64_t wide_row = int64_t(1) << 25;
+  if (a.ks == 3 && a.Cin % 32 == 0 && int64_t(a.W) * a.Cin < wide_row &&
+      int64_t(a.W) * a.Cout < wide_row && int64_t(a.B) * a.H * a.W < (int64_t(1) << 31)) {
     const int tw = a.W >= 64 ? 64 : a.W >= 32 ? 32 : 16;
     const int rows = (wide ? 128 : 256) / tw;
     p.kind = (wide ? 0 : 3) + (tw == 64 ? 0 : tw == 32 ? 1 : 2);
@@ -1835,12 +1927,12 @@ hipError_t nn_conv_wgrad(const NnWgradArgs& a, hipStream_t s, int phases) {
   if (a.part && a.part_cap < nn_conv_wgrad_part_floats(a)) return hipErrorInvalidValue;
   const dim3 grid(p.gx, p.gy, p.gz), block(256);
   if (phases & 1) switch (p.kind) {
-    case 0: hipLaunchKernelGGL((k_conv3_wgrad<64, 64, 2>), grid, block, 0, s, a); break;
-    case 1: hipLaunchKernelGGL((k_conv3_wgrad<64, 32, 4>), grid, block, 0, s, a); break;
-    case 2: hipLaunchKernelGGL((k_conv3_wgrad<64, 16, 8>), grid, block, 0, s, a); break;
-    case 3: hipLaunchKernelGGL((k_conv3_wgrad<32, 64, 4>), grid, block, 0, s, a); break;
-    case 4: hipLaunchKernelGGL((k_conv3_wgrad<32, 32, 8>), grid, block, 0, s, a); break;
-    case 5: hipLaunchKernelGGL((k_conv3_wgrad<32, 16, 16>), grid, block, 0, s, a); break;
+    case 0: launch_conv3_wgrad<64, 64, 2>(a, grid, s); break;
+    case 1: launch_conv3_wgrad<64, 32, 4>(a, grid, s); break;
+    case 2: launch_conv3_wgrad<64, 16, 8>(a, grid, s); break;
+    case 3: launch_conv3_wgrad<32, 64, 4>(a, grid, s); break;
+    case 4: launch_conv3_wgrad<32, 32, 8>(a, grid, s); break;
+    case 5: launch_conv3_wgrad<32, 16, 16>(a, grid, s); break;
     case 6: hipLaunchKernelGGL((k_conv_wgrad<3, 64, 64>), grid, block, 0, s, a); break;
     case 7: hipLaunchKernelGGL((k_conv_wgrad<3, 32, 64>), grid, block, 0, s, a); break;
     case 8: hipLaunchKernelGGL((k_conv_wgrad<1, 64, 64>), grid, block, 0, s, a); break;
