@@ -264,7 +264,8 @@ cpi_status check_refocus_args(const float* gamma, const cpi_geometry* g, const d
 }
 
 cpi_status enqueue_tables(const cpi_geometry* g, const double* alphas, int32_t n_alpha,
-                          const cpi::RefocusPlan& pl, uint8_t* ws, hipStream_t st) {
+                          const cpi::RefocusPlan& pl, uint8_t* ws, hipStream_t st,
+                          bool rows = true) {
   const cpi::RefGeom rg = ref_geom(g);
   int32_t* itab = reinterpret_cast<int32_t*>(ws + pl.off_itab);
   float* ftab = reinterpret_cast<float*>(ws + pl.off_ftab);
@@ -272,7 +273,7 @@ cpi_status enqueue_tables(const cpi_geometry* g, const double* alphas, int32_t n
   for (int first = 0; first < n_alpha; first += cpi::kAlphaPerLaunch) {
     const int cnt = (n_alpha - first) < cpi::kAlphaPerLaunch ? n_alpha - first : cpi::kAlphaPerLaunch;
     CPI_HIP(cpi::refocus_tables(rg, alphas, first, cnt, pl.table_stride, itab, ftab,
-                                ws + pl.off_ytab, st),
+                                rows ? ws + pl.off_ytab : nullptr, st),
             "refocus tables");
   }
   return CPI_OK;
@@ -290,11 +291,17 @@ cpi_status refocus_enqueue(const float* gamma, const cpi_geometry* g, const doub
   cpi_status s = check_refocus_args(gamma, g, alphas, n_alpha, out, workspace, ws_bytes, &pl);
   if (s != CPI_OK) return s;
   uint8_t* ws = static_cast<uint8_t*>(workspace);
-  s = enqueue_tables(g, alphas, n_alpha, pl, ws, st);
-  if (s != CPI_OK) return s;
   const RefGeom rg = ref_geom(g);
+  const bool gather = !plain && !forced && refocus_gather_fits(rg, n_alpha);
+  s = enqueue_tables(g, alphas, n_alpha, pl, ws, st, !gather);
+  if (s != CPI_OK) return s;
   const int32_t* itab = reinterpret_cast<const int32_t*>(ws + pl.off_itab);
   const float* ftab = reinterpret_cast<const float*>(ws + pl.off_ftab);
+  if (gather) {
+    ProfScope ps("refocus_batched", st);
+    CPI_HIP(refocus_gather(gamma, rg, itab, ftab, pl.table_stride, n_alpha, out, st), "refocus");
+    return CPI_OK;
+  }
   if (plain || g->wa < 2 || g->ha < 2) {
     ProfScope ps("refocus_plain", st);
     for (int k = 0; k < n_alpha; ++k)
@@ -376,15 +383,21 @@ cpi_status refocus_enqueue_config(const float* gamma, const cpi_geometry* g, con
     return set_error(CPI_ERR_WORKSPACE, "refocus workspace too small: need " +
                                             std::to_string(need) + " bytes");
   uint8_t* ws = static_cast<uint8_t*>(workspace);
-  s = enqueue_tables(g, alphas, n_alpha, pl, ws, st);
-  if (s != CPI_OK) return s;
   const RefGeom rg = ref_geom(g);
+  const bool gather = refocus_gather_fits(rg, n_alpha);   // as refocus_enqueue takes it
+  s = enqueue_tables(g, alphas, n_alpha, pl, ws, st, !gather);
+  if (s != CPI_OK) return s;
   const int32_t* itab = reinterpret_cast<const int32_t*>(ws + pl.off_itab);
   const float* ftab = reinterpret_cast<const float*>(ws + pl.off_ftab);
   if (g->wa < 2 || g->ha < 2) {
     ProfScope ps("refocus_plain", st);
     for (int k = 0; k < n_alpha; ++k)
       CPI_HIP(refocus_plain(gamma, rg, itab, ftab, pl.table_stride, k, out, st), "refocus");
+    return CPI_OK;
+  }
+  if (gather) {
+    ProfScope ps("refocus_batched", st);
+    CPI_HIP(refocus_gather(gamma, rg, itab, ftab, pl.table_stride, n_alpha, out, st), "refocus");
     return CPI_OK;
   }
   ProfScope ps("refocus_batched", st);
