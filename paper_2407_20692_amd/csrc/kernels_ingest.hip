@@ -96,8 +96,10 @@ constexpr int kBitsTileFr = 512;     // frames per tile (16 words of a bit row)
 constexpr int kBitsLdsCol = 1060;
 
 // Packed-bit frames -> bit rows, for the 512-frame tiles that lie wholly
-// below n, when frame rows are a multiple of 4 bytes long (k_ingest_bits_tail
-// writes the rest).  A work-group (4 waves) owns 1024 pixels and a slice of
+// below n (k_ingest_bits_tail writes the rest).  WORDS: frame rows are a
+// multiple of 4 bytes long; else words are loaded from any byte (one load all
+// the same), and a row's last word, of 1 to 3 bytes, as the row's last four
+// bytes, shifted: no byte outside the row is read.  A work-group (4 waves) owns 1024 pixels and a slice of
 // those tiles.  For each tile, each half-wave takes 32
 // frames: lane q of the half reads word q of the tile's row segment in each
 // of the 32 frames (a half reads 128 contiguous bytes per frame) and
@@ -105,6 +107,7 @@ constexpr int kBitsLdsCol = 1060;
 // frame bits of pixels 32 q .. 32 q + 31.  The words go to LDS and are
 // written out as 64-byte row segments (four lanes per row, 16 bytes each).  Per-pixel popcounts are kept in registers,
 // combined in LDS, and added to sums once per work-group.
+template <bool WORDS>
 __global__ __launch_bounds__(256, 2) void k_ingest_bits(IngestJob j0, IngestJob j1, int64_t groups0,
                                                     int64_t n, int64_t kw, int64_t ntiles,
                                                     int64_t tiles_per_slice) {
@@ -140,12 +143,28 @@ __global__ __launch_bounds__(256, 2) void k_ingest_bits(IngestJob j0, IngestJob 
   // word and are masked to zero.  (Offsets stay below 2^31: rows are under
   // 2^22 bytes.)
   const bool word_in = byte + 4 <= fbytes;
-  const uint32_t word_mask = word_in ? 0xffffffffu : 0u;
+  const bool part_in = !WORDS && !word_in && byte < fbytes;   // (rows of at least 4 bytes)
+  const uint32_t word_mask = word_in || part_in ? 0xffffffffu : 0u;
+  const int part_shift = part_in ? 8 * int(byte + 4 - fbytes) : 0;
   int voff[2];
 #pragma unroll
   for (int pass = 0; pass < 2; ++pass)
-    voff[pass] = int((8 * pass + 2 * wave + half) * 32 * fbytes + (word_in ? byte : 0));
+    voff[pass] = int((8 * pass + 2 * wave + half) * 32 * fbytes +
+                     (word_in ? byte : part_in ? fbytes - 4 : 0));
   auto load_tile = [&](int64_t kt, uint32_t(&d)[2][32]) {
+    if constexpr (!WORDS) {
+      struct __attribute__((packed)) AnyWord {
+        uint32_t v;
+      };
+      const uint8_t* tile = frames + kt * kBitsTileFr * fbytes;
+#pragma unroll
+      for (int pass = 0; pass < 2; ++pass)
+#pragma unroll
+        for (int k = 0; k < 32; ++k)
+          d[pass][k] = reinterpret_cast<const AnyWord*>(tile + k * fbytes +
+                                                        uint32_t(voff[pass]))->v;
+      return;
+    }
     const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint8_t*>(frames + kt * kBitsTileFr * fbytes), short(0), 0x7fffffff,
         0x00020000);
@@ -173,6 +192,9 @@ __global__ __launch_bounds__(256, 2) void k_ingest_bits(IngestJob j0, IngestJob 
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
       const int fw = 8 * pass + 2 * wave + half;
+      if constexpr (!WORDS)
+#pragma unroll
+        for (int k = 0; k < 32; ++k) cur[pass][k] = (cur[pass][k] >> part_shift) & word_mask;
       transpose32(cur[pass]);
 #pragma unroll
       for (int i = 0; i < 32; ++i) {
@@ -616,7 +638,17 @@ hipError_t ingest_bits(const IngestJob& a, const IngestJob& b, int64_t n, int64_
   if (kpad_bits % kBitsTileFr != 0 || n > kpad_bits || kpad_bits / 32 >= (int64_t(1) << 19))
     return hipErrorInvalidValue;
   const bool aligned = (((a.npix + 7) / 8) & 3) == 0 && (((b.npix + 7) / 8) & 3) == 0;
-  const int64_t full = aligned ? n / kBitsTileFr : 0;   // tiles for the tile kernel
+  // tiles for the tile kernel: with rows of whole words, and with others from 6
+  // MiB of frames on, below which the tail kernel's short threads, in one
+  // launch, are as fast.  Whole calls, tail kernel alone / with tiles, us, Da and
+  // Db of 7575 and 1353 pixels: 4200 frames (4.7 MB) 82 / 88, 12345 (13.8 MB)
+  // 149 / 120, 50000 485 / 294; 40007 and 2001 pixels: 1100 frames (5.8 MB)
+  // 213 / 220, 2100 (11 MB) 250 / 241, 12345 695 / 502; 4225 and 1089 pixels:
+  // 12345 frames (8.2 MB) 110 / 101.
+  const int64_t row_bytes = (a.npix + 7) / 8 + (b.npix + 7) / 8;
+  const bool any = (a.npix + 7) / 8 >= 4 && (b.npix + 7) / 8 >= 4 &&
+                   n >= (int64_t(6) << 20) / row_bytes;
+  const int64_t full = aligned || any ? n / kBitsTileFr : 0;
   const int64_t groups0 = (a.npix_pad + kBitsTilePix - 1) / kBitsTilePix;
   const int64_t groups = groups0 + (b.npix_pad + kBitsTilePix - 1) / kBitsTilePix;
   if (groups > 0x7fffffff) return hipErrorInvalidValue;
@@ -624,8 +656,9 @@ hipError_t ingest_bits(const IngestJob& a, const IngestJob& b, int64_t n, int64_
     const int64_t slices = slices_for(groups, full, 2048);
     const int64_t tps = (full + slices - 1) / slices;
     const int64_t used = (full + tps - 1) / tps;
-    hipLaunchKernelGGL(k_ingest_bits, dim3(unsigned(groups), unsigned(used)), dim3(256), 0, s, a,
-                       b, groups0, n, kpad_bits / 32, full, tps);
+    hipLaunchKernelGGL(aligned ? k_ingest_bits<true> : k_ingest_bits<false>,
+                       dim3(unsigned(groups), unsigned(used)), dim3(256), 0, s, a, b, groups0, n,
+                       kpad_bits / 32, full, tps);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
