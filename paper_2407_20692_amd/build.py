@@ -27,6 +27,7 @@ SOURCES = [
     "kernels_refocus.hip",
     "kernels_refocus_rows.hip",
     "kernels_refocus_window.hip",
+    "kernels_refocus_gather.hip",
     "autotune.hip",
     "peaks.hip",
     "kernels_nn.hip",

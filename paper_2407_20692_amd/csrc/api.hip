@@ -292,7 +292,7 @@ cpi_status refocus_enqueue(const float* gamma, const cpi_geometry* g, const doub
   if (s != CPI_OK) return s;
   uint8_t* ws = static_cast<uint8_t*>(workspace);
   const RefGeom rg = ref_geom(g);
-  const bool gather = !plain && !forced && refocus_gather_fits(rg, n_alpha);
+  const bool gather = !plain && !forced && refocus_gather_fits(rg, n_alpha, false);
   s = enqueue_tables(g, alphas, n_alpha, pl, ws, st, !gather);
   if (s != CPI_OK) return s;
   const int32_t* itab = reinterpret_cast<const int32_t*>(ws + pl.off_itab);
@@ -350,6 +350,11 @@ cpi_status refocus_enqueue(const float* gamma, const cpi_geometry* g, const doub
                        "row-lane refocus does not take this geometry or plane set");
     c = default_sep_config(g, n_alpha);
   }
+  if (!forced && refocus_gather_fits(rg, n_alpha, true)) {
+    ProfScope ps("refocus_batched", st);
+    CPI_HIP(refocus_gather(gamma, rg, itab, ftab, pl.table_stride, n_alpha, out, st), "refocus");
+    return CPI_OK;
+  }
   ProfScope ps("refocus_batched", st);
   CPI_HIP(refocus_batched(gamma, rg, itab, ftab, ws + pl.off_ytab, ws + pl.off_bounds,
                           pl.table_stride, n_alpha, c, partial, out, st),
@@ -384,7 +389,7 @@ cpi_status refocus_enqueue_config(const float* gamma, const cpi_geometry* g, con
                                             std::to_string(need) + " bytes");
   uint8_t* ws = static_cast<uint8_t*>(workspace);
   const RefGeom rg = ref_geom(g);
-  const bool gather = refocus_gather_fits(rg, n_alpha);   // as refocus_enqueue takes it
+  const bool gather = refocus_gather_fits(rg, n_alpha, true);   // as refocus_enqueue takes it
   s = enqueue_tables(g, alphas, n_alpha, pl, ws, st, !gather);
   if (s != CPI_OK) return s;
   const int32_t* itab = reinterpret_cast<const int32_t*>(ws + pl.off_itab);

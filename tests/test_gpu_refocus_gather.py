@@ -1,7 +1,8 @@
 """GPU parity of the one-launch refocus of small stacks: fewer, as many and more
 lens-plane columns than its 16 threads per pixel, output sizes that are no
 multiple of its 16 pixels, samples outside the views, the most views its LDS
-holds and one more (which the batched kernel takes), and the same in work.
+holds and one more (which the batched kernel takes), and the same in work and,
+above that work, in planes.
 Graded like every refocus by max |I_gpu - I_oracle| / max |I_oracle| <= 1e-5 per
 plane, on a seeded random FP32 Gamma."""
 import numpy as np
@@ -24,6 +25,11 @@ CASES = [
     (_geo(4, 4, 1023, 2), np.linspace(0.7, 1.3, 3)),
     (_geo(32, 32, 16, 16), np.linspace(0.5, 1.5, 64)),
     (_geo(32, 32, 16, 16), np.linspace(0.5, 1.5, 65)),
+    # few planes at any size, with too wide a spread for the row-lane kernels,
+    # and one more than those
+    (_geo(128, 128, 32, 32), np.array([0.5, 1.5])),
+    (_geo(40, 90, 33, 50), np.linspace(0.5, 1.5, 8)),
+    (_geo(40, 90, 33, 50), np.linspace(0.5, 1.5, 9)),
     # planes whose samples leave the view on most columns and rows
     (oracle.Geometry(24, 20, 4, 4, 30.0, 30.0, 11.5, 9.5, 1.5, 1.5, 24, 20),
      np.linspace(0.5, 0.6, 6)),
