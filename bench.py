@@ -74,7 +74,7 @@ PAPER_LIKE_KEY = ("da128_db64_n20000", "da128_db64_32planes")
 LARGE_KEY = ("da256_db128_n100000", "da256_db128_128planes")
 GEMM_SOURCE = os.path.join(ROOT, "paper_2407_20692_amd", "csrc", "kernels_gemm.hip")
 REF_SOURCE = os.path.join(ROOT, "paper_2407_20692_amd", "csrc", "kernels_refocus.hip")
-ROWS_SOURCE = os.path.join(ROOT, "paper_2407_20692_amd", "csrc", "kernels_refocus_rows.hip")
+ROWS_SOURCE = os.path.join(ROOT, "paper_2407_20692_amd", "csrc", "kernels_refocus_window.hip")
 
 
 def log(msg):
@@ -770,9 +770,9 @@ def refocus_roofline(cpi, geo, alphas, launch_ms, traffic_key):
     source = ROWS_SOURCE if rows else REF_SOURCE
     traffic = measured_traffic(summary, source, tiles)
     r = {
-        "kernel": ("k_ref_rows + k_ref_rows_fold (row-lane x pass: lanes are view rows, window "
-                   "staged column by column in LDS, column cells and weights from a per-view "
-                   "table; then the fold over y_b)" if rows else
+        "kernel": ("k_ref_window + k_ref_rows_fold (row-lane x pass: lanes are view rows, the "
+                   "view's window in registers, taps picked by the VGPR index mode, weights by "
+                   "DPP broadcast; then the fold over y_b)" if rows else
                    "k_ref_sep (planes batched per work-group, LDS-staged view windows, column "
                    "interpolants summed over x_b before the row weights)" if tiles[3] == 1 else
                    "k_ref_batched (planes batched per work-group, LDS-staged view windows)"),

@@ -165,7 +165,7 @@ struct RefocusConfig {
   int splits = 1;    // view-row splits (partial sums reduced afterwards)
   int mode = 0;      // 0: per-row interpolation (k_ref_batched); 1: column sums over x_b
                      // first, row weights once per y_b (k_ref_sep); 2: row-lane x pass
-                     // and fold (k_ref_rows), with kp planes x rw output columns per
+                     // and fold (k_ref_window or k_ref_rows), with kp planes x rw output columns per
                      // work-group (splits and stages unused)
   int stages = 3;    // mode 1: view windows staged in LDS (2, 3 or 4)
 };
