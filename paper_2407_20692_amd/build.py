@@ -21,6 +21,7 @@ LIB = os.path.join(HERE, "libcpi.so")
 ARCH = "gfx950"
 SOURCES = [
     "plan.cpp",
+    "refocus_window_plan.cpp",
     "kernels_ingest.hip",
     "kernels_gemm.hip",
     "kernels_f32.hip",

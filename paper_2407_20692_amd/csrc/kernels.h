@@ -7,6 +7,7 @@
 #include <cstdint>
 
 #include "plan.h"
+#include "refocus_window_plan.h"
 
 namespace cpi {
 
@@ -139,11 +140,6 @@ hipError_t sgemm_gamma(const float* fb, const float* fa, int64_t kpad, int64_t p
                        const float* sb, int layout, float* out, hipStream_t s);
 
 // ---- refocus -------------------------------------------------------------
-struct RefGeom {
-  int wa, ha, wb, hb, out_w, out_h;
-  double mag_x, mag_y, ca_x, ca_y, cb_x, cb_y;
-};
-
 // Per-plane coordinate tables for planes [first, first+count), count <= 64:
 // integer parts and FP32 fractions of a_x, a_y, b_x, b_y; and, if ytab is
 // not null, the row table of the batched kernel (16 bytes per plane, y_b, y_r).
@@ -204,16 +200,8 @@ hipError_t refocus_rows(const float* gamma, const RefGeom& g, const double* alph
                         int n_alpha, int na, int xr, const RowsWorkspace& w, float* out,
                         hipStream_t s);
 
-// Register-window x pass of the row-lane refocus: work split chosen for a
-// geometry and plane set (host), and the pass over one chunk of planes
+// Register-window x pass of the row-lane refocus over one chunk of planes
 // (column tables, then T; row ranges yr as for groups of na planes).
-struct WindowSplit {
-  int np = 0, xc = 0, pg = 0;   // planes x columns per wave, plane groups per work-group
-  int na = 0, xr = 0;           // planes x columns per work-group
-  int blocks = 0;               // 16-column blocks its windows take
-};
-bool window_split(const RefGeom& g, const double* alphas, int n_alpha, int64_t chunk,
-                  WindowSplit* out);
 hipError_t window_xpass(const float* gamma, const RefGeom& g, const double* alphas,
                         const WindowSplit& w, const int32_t* itab, const float* ftab,
                         int64_t stride, int first, int count, int32_t* xe, const int2* yr,

@@ -45,7 +45,7 @@
 // registers that a narrow one leaves, nothing.
 #include <hip/hip_runtime.h>
 
-#include <cmath>
+#include <algorithm>
 
 #include "kernels.h"
 #include "refocus_common.h"
@@ -54,14 +54,6 @@ namespace cpi {
 
 namespace {
 
-constexpr int kWinSlots = 2;         // 64-row units per work-group, one row of each per lane
-constexpr int kWinWaves = 4;         // waves per work-group
-constexpr int kWinPairs = 64;        // (plane, column) pairs per wave
-constexpr int kWinCols = 40;         // window columns a wave keeps in registers
-constexpr int kWinBlocks = 9;        // 16-column blocks (8 KB each) that the LDS holds
-constexpr int kWinBlockBytes = kWinSlots * 64 * 16 * 4;
-constexpr int kWinLds = kWinBlocks * kWinBlockBytes;
-constexpr int kWinMaxStages = 3;     // views staged at a time at most
 constexpr int kWinWaveWords = 176;   // table words per wave and view
 constexpr int kWinTabBytes = kWinWaves * 512;   // of which the weights are staged in LDS
 constexpr int kWinMaxGroups = 64;    // plane groups per chunk (256 planes in groups of 4 or more)
@@ -76,7 +68,7 @@ constexpr int kWinMaxGroups = 64;    // plane groups per chunk (256 planes in gr
 //     its cell's column in the wave's window, and the bit that puts the index on
 //     the second operand;
 //   words 160 .. 164: where the wave's first four 4-column chunks start in the
-//     staged window (16-bit LDS offsets, to be exchanged (xor) with the lane's);
+//     staged window (window_pack_chunks; to be exchanged (xor) with the lane's offset);
 //     its number of chunks and, from bit 8, one bit per 16 pairs with a nonzero
 //     weight; the work-group's first staged column (a multiple of 4) and number
 //     of 16-column blocks staged;
@@ -151,8 +143,7 @@ __global__ __launch_bounds__(256) void k_window_xtab(GeomI g, const int32_t* __r
     int bits = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) bits |= ((lives >> (16 * j)) & 0xffffu) ? 1 << j : 0;
-    auto at = [](int q) { return uint32_t((q >> 2) * kWinBlockBytes | (q & 3) << 4); };
-    const int xa = int(at(q0) | at(q0 + 1) << 16), xc = int(at(q0 + 2) | at(q0 + 3) << 16);
+    const int xa = int(window_pack_chunks(q0)), xc = int(window_pack_chunks(q0 + 2));
     const int nl = nq | bits << 8;
     e[160] = xa;
     e[161] = xc;
@@ -481,10 +472,10 @@ __global__ __launch_bounds__(64 * kWinWaves, 2) void k_ref_window(
       const int xa = head[0], xc = head[1];
       const int nq = head[2] & 0xff, live = head[2] >> 8;
       const uint32_t sb = base + uint32_t(stage * stage_bytes);
-      const uint32_t a0 = (rd ^ uint32_t(xa & 0xffff)) + sb;
-      const uint32_t a1 = (rd ^ (uint32_t(xa) >> 16)) + sb;
-      const uint32_t a2 = (rd ^ uint32_t(xc & 0xffff)) + sb;
-      const uint32_t a3 = (rd ^ (uint32_t(xc) >> 16)) + sb;
+      const uint32_t a0 = (rd ^ window_unpack_chunk(uint32_t(xa), 0)) + sb;
+      const uint32_t a1 = (rd ^ window_unpack_chunk(uint32_t(xa), 1)) + sb;
+      const uint32_t a2 = (rd ^ window_unpack_chunk(uint32_t(xc), 0)) + sb;
+      const uint32_t a3 = (rd ^ window_unpack_chunk(uint32_t(xc), 1)) + sb;
       const uint32_t tw = tab0 + uint32_t(stage * kWinTabBytes) + uint32_t(16 * (lane & 15));
       i8v next;
       asm volatile(CPI_WIN_VIEW
@@ -564,72 +555,6 @@ __global__ __launch_bounds__(64 * kWinWaves, 2) void k_ref_window(
 #undef CPI_WIN_ACC
 #undef CPI_WIN_CLOBBERS
 
-// One axis of the geometry.
-struct Axis {
-  double mag, ca, cb;
-  int na, nb, out;   // detector-A, detector-B and output sizes
-};
-
-// Most samples that the cells of planes [p0, p1) and output pixels [x0, x1]
-// span on an axis at any lens-plane position, from the first cell's to the
-// last cell's second sample.  u = alpha (x_r - ca) + ca + (1 - alpha) mag (x_b - cb)
-// is bilinear in (alpha, x_r), so the samples lie between its values at the
-// four corners (alpha_min or alpha_max, first or last pixel).  Along x_b the
-// corners are straight lines: where the view's edges do not cut them their
-// largest distance is a convex function, and where one edge does, it still
-// is, so it is largest at an end of the x_b range or where a corner crosses
-// an edge.
-int axis_span(const Axis& g, const double* alphas, int p0, int p1, int x0, int x1) {
-  const double s0 = g.mag * (0 - g.cb), s1 = g.mag * (g.nb - 1 - g.cb);
-  const double smin = std::fmin(s0, s1), smax = std::fmax(s0, s1);
-  double al[2] = {alphas[p0], alphas[p0]};
-  for (int k = p0; k < p1; ++k) {
-    al[0] = std::fmin(al[0], alphas[k]);
-    al[1] = std::fmax(al[1], alphas[k]);
-  }
-  double c0[4], c1[4];   // corner i: u = c0 + c1 s
-  for (int i = 0; i < 4; ++i) {
-    c0[i] = al[i >> 1] * ((i & 1 ? x1 : x0) - g.ca) + g.ca;
-    c1[i] = 1.0 - al[i >> 1];
-  }
-  int need = 0;
-  for (int k = 0; k < 10; ++k) {
-    double s = k == 8 ? smin : smax;
-    if (k < 8) {
-      const int i = k >> 1;
-      if (c1[i] == 0.0) continue;
-      s = ((k & 1 ? double(g.na) : -1.0) - c0[i]) / c1[i];
-      if (!(s > smin && s < smax)) continue;
-    }
-    double lo = 1e300, hi = -1e300;
-    for (int i = 0; i < 4; ++i) {
-      const double u = c0[i] + c1[i] * s;
-      lo = std::fmin(lo, u);
-      hi = std::fmax(hi, u);
-    }
-    lo = std::fmax(lo, -1.0);
-    hi = std::fmin(hi, double(g.na));
-    // (the device's coordinates are within 2^-22 of these)
-    if (hi >= lo) need = std::max(need, int(hi - lo + 1e-5) + 3);
-  }
-  return need;
-}
-
-// the most over all groups of na planes and tiles of xr output columns
-int window_span(const RefGeom& g, const double* alphas, int n_alpha, int na, int xr) {
-  const Axis x{g.mag_x, g.ca_x, g.cb_x, g.wa, g.wb, g.out_w};
-  int need = 0;
-  for (int p = 0; p < n_alpha; p += na)
-    for (int c = 0; c < g.out_w; c += xr)
-      need = std::max(need, axis_span(x, alphas, p, std::min(p + na, n_alpha), c,
-                                      std::min(c + xr, g.out_w) - 1));
-  return need;
-}
-
-// 16-column blocks that windows of `cols` columns take, starting at a
-// multiple of 4 columns
-int staged_blocks(int cols) { return (cols + 3 + 15) / 16; }
-
 template <int NP, int XC, int PG>
 hipError_t launch_window(const float* gamma, const RefGeom& g, const double* alphas,
                          const int32_t* itab, const float* ftab, int64_t stride, int first,
@@ -643,11 +568,8 @@ hipError_t launch_window(const float* gamma, const RefGeom& g, const double* alp
   if (nx > 0x7fffffff || groups > kWinMaxGroups) return hipErrorInvalidValue;
   WindowUnits units = {};
   int per_yb = 1;   // work-groups of a lens-plane row at most
-  const Axis y{g.mag_y, g.ca_y, g.cb_y, g.ha, g.hb, g.out_h};
   for (int q = 0; q < groups; ++q) {
-    const int rows = std::min(g.ha, axis_span(y, alphas, first + q * NA,
-                                              first + std::min((q + 1) * NA, count), 0,
-                                              g.out_h - 1));
+    const int rows = window_rows(g, alphas, first + q * NA, first + std::min((q + 1) * NA, count));
     if ((rows + 63) / 64 > 255) return hipErrorInvalidValue;
     units.n[q] = uint8_t(std::max(1, (rows + 63) / 64));
     per_yb = std::max(per_yb, (units.n[q] + kWinSlots - 1) / kWinSlots);
@@ -666,41 +588,6 @@ hipError_t launch_window(const float* gamma, const RefGeom& g, const double* alp
 }
 
 }  // namespace
-
-bool window_split(const RefGeom& g, const double* alphas, int n_alpha, int64_t chunk,
-                  WindowSplit* out) {
-  // byte offsets within a view stay below 2^31, units per y_b below 256
-  if (chunk < 16 || chunk % 16 != 0 || g.wa < 2 || g.ha < 2 || g.ha > 255 * 64 ||
-      int64_t(g.wa) * g.ha >= (int64_t(1) << 29))
-    return false;
-  // Of the shapes of a wave (planes x columns) and arrangements of the four
-  // waves, the one that moves the fewest window columns per pair: those
-  // staged once per work-group, and those each wave then reads (3 columns
-  // more: windows start at multiples of 4).
-  struct Shape {
-    int np, xc, pg;
-  };
-  double best = -1.0;
-  for (const Shape& c : {Shape{8, 8, 2}, Shape{4, 16, 2}, Shape{4, 16, 1}}) {
-    const int na = c.np * c.pg, xr = c.xc * (kWinWaves / c.pg);
-    const int mine = window_span(g, alphas, n_alpha, c.np, c.xc) + 3;
-    if (mine > kWinCols) continue;
-    const int span = window_span(g, alphas, n_alpha, na, xr);
-    if (staged_blocks(span) > kWinBlocks) continue;
-    const double cost = (double(span + 3) / (4 * kWinPairs) + double(mine) / kWinPairs) *
-                        ((n_alpha + na - 1) / na * na) * ((g.out_w + xr - 1) / xr * xr);
-    if (best < 0 || cost < best) {
-      best = cost;
-      out->np = c.np;
-      out->xc = c.xc;
-      out->pg = c.pg;
-      out->na = na;
-      out->xr = xr;
-      out->blocks = staged_blocks(span);
-    }
-  }
-  return best >= 0;
-}
 
 hipError_t window_xpass(const float* gamma, const RefGeom& g, const double* alphas,
                         const WindowSplit& w, const int32_t* itab, const float* ftab,
