@@ -211,7 +211,7 @@ __global__ __launch_bounds__(256) void k_window_xtab(GeomI g, const int32_t* __r
   "buffer_load_dwordx4 %[from], %[rs], 0 offen offset:" #o " lds\n"     \
   "s_add_u32 m0, %[dst], 8128*" #i "+1024\n"                            \
   "s_nop 0\n"                                                           \
-  "buffer_load_dwordx4 %[from], %[rs], %[j1] offen offset:" #o " lds\n"
+  "buffer_load_dwordx4 %[from1], %[rs], 0 offen offset:" #o " lds\n"
 #define CPI_WIN_COPIES \
   CPI_WIN_COPY(0, 0) \
   CPI_WIN_COPY(1, 64) \
@@ -423,9 +423,8 @@ __global__ __launch_bounds__(64 * kWinWaves, 2) void k_ref_window(
     const bool mine = unit(u0 + wave / 2, &yb, &row, &row_last);
     const int pa = g.wa * g.ha;
     const float* view = gamma + (mine ? int64_t(yb) * g.wb * pa : 0);
-    const int cr = lane >> 2, cc = (lane & 3) ^ ((lane >> 4) & 3);
-    const uint32_t from = uint32_t(((row + 32 * (wave & 1) + cr) * g.wa + 4 * cc) * 4);
-    const uint32_t j1 = uint32_t(64 * g.wa);   // 16 rows down
+    const uint32_t from = window_lane_offset(row, wave, lane, 0, g.wa);
+    const uint32_t from1 = window_lane_offset(row, wave, lane, 1, g.wa);
     const uint32_t base = uint32_t(reinterpret_cast<uintptr_t>(ring));
     const uint32_t rd = uint32_t(64 * (lane & 15) + 1024 * (lane >> 4) + 16 * ((lane >> 2) & 3));
     const uint32_t tl = uint32_t(16 * (lane & 31));
@@ -451,7 +450,7 @@ __global__ __launch_bounds__(64 * kWinWaves, 2) void k_ref_window(
       asm volatile("s_nop 4\n" CPI_WIN_COPIES "Lcopy%=:\n" CPI_WIN_TABLE
                    :
                    : [nb] "s"(nb), [dst] "s"(base + uint32_t(k * stage_bytes + 2048 * wave)),
-                     [rs] "s"(rs), [from] "v"(from), [j1] "s"(j1),
+                     [rs] "s"(rs), [from] "v"(from), [from1] "v"(from1),
                      [td] "s"(tab0 + uint32_t(k * kWinTabBytes)), [tl] "v"(tl),
                      [tp] "s"(tp + kk * kStep)
                    : "scc", "memory");
@@ -483,7 +482,7 @@ __global__ __launch_bounds__(64 * kWinWaves, 2) void k_ref_window(
                    : [fly] "s"(fly), [nq] "s"(nq), [nb] "s"(nb), [spaces] "s"(stages),
                      [dst] "s"(base + uint32_t(to * stage_bytes + 2048 * wave)), [rs] "s"(rs),
                      [live] "s"(live), [a0] "v"(a0), [a1] "v"(a1), [a2] "v"(a2), [a3] "v"(a3),
-                     [from] "v"(from), [j1] "s"(j1),
+                     [from] "v"(from), [from1] "v"(from1),
                      [td] "s"(tab0 + uint32_t(to * kWinTabBytes)), [tl] "v"(tl), [tp] "s"(tp),
                      [th] "s"(th), [tn] "s"(tn), [tw] "v"(tw)
                    : CPI_WIN_CLOBBERS);

@@ -39,6 +39,19 @@ constexpr uint32_t window_unpack_chunk(uint32_t word, int k) {
 static_assert((window_chunk_at(4 * kWinBlocks + 2) >> 4) <= 0xffffu,
               "chunk offsets fit their field");
 
+// Byte offset, from a view's first staged column, of what lane `lane` of wave
+// `wave` copies of each block's half `half`: four columns of one view row, of 16
+// rows per half and two halves per wave, the unit's first row being `row`.  The
+// whole row goes into this lane offset, so that rows past the view lie past the
+// view's buffer descriptor, which then delivers zeros.  (A scalar offset for the
+// second half would not be sure to count in that check, nor could it be taken
+// off the descriptor's size where views have fewer than 16 rows.)
+constexpr uint32_t window_lane_offset(int row, int wave, int lane, int half, int wa) {
+  return uint32_t((row + 32 * (wave & 1) + 16 * half + (lane >> 2)) * wa +
+                  4 * ((lane & 3) ^ ((lane >> 4) & 3))) *
+         4u;
+}
+
 // Work split of the pass for a geometry and plane set, planes in chunks of
 // `chunk`; false if it does not take them.
 struct WindowSplit {

@@ -2,7 +2,7 @@
 // spaced, clustered, unordered and drawn plane lists, the windows of every
 // work-group and wave at every view, as the column table forms them, lie in
 // what the plan stages, and the chunk offsets read back from the table are
-// those of the chunks.  Built with the sanitizers.
+// those of the chunks; and copies of rows past a view are out of its bounds.  Built with the sanitizers.
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
@@ -84,6 +84,26 @@ static bool walk(const RefGeom& g, const std::vector<double>& al, WindowSplit* u
   return true;
 }
 
+// Copies of views of every height around a wave's rows: what the buffer
+// descriptor checks (the lane offset and the instruction's) is at or past the
+// view's records exactly where the row is past the view.
+static void copies(int wa, int ha) {
+  for (int wx0 = 0; wx0 < wa - 1; wx0 += 4 * (1 + wa / 9)) {
+    const uint32_t records = uint32_t(wa * ha - wx0) * 4;
+    for (int row = 0; row < ha; row += 1 + ha / 7)
+      for (int wave = 0; wave < kWinWaves; ++wave)
+        for (int lane = 0; lane < 64; ++lane)
+          for (int half = 0; half < 2; ++half) {
+            const int r = row + 32 * (wave & 1) + 16 * half + (lane >> 2);
+            const uint32_t at = window_lane_offset(row, wave, lane, half, wa);
+            if (r >= ha) CHECK(at >= records);
+            // (columns past the row's end are the next row's)
+            if (r < ha - 1 && wx0 + 16 * kWinBlocks <= wa)
+              CHECK(at + 64 * (kWinBlocks - 1) + 16 <= records);
+          }
+  }
+}
+
 static std::vector<double> clusters(double a, double b, double step, int each) {
   std::vector<double> v;
   for (double c : {a, b})
@@ -92,6 +112,8 @@ static std::vector<double> clusters(double a, double b, double step, int each) {
 }
 
 int main() {
+  for (int ha : {2, 3, 8, 15, 16, 17, 31, 33, 47, 63, 64, 65, 100, 128, 200})
+    for (int wa : {64, 65, 150, 256}) copies(wa, ha);
   // evenly spaced planes
   for (int n : {1, 5, 16, 33, 128}) {
     std::vector<double> al;
