@@ -346,6 +346,17 @@ struct Pass {
     w.low = low;
     w.c_low = low ? c_low : 0;
     w.pool_in = pool_in ? 1 : 0;
+    if ((low || pool_in) && !cpi::nn_conv_wgrad_takes_low(w)) {
+      // the input written out first, into the forward pass's space for it
+      const int lv = pool_in ? L.level - 1 : L.level;
+      w.in = pool_in ? n.pool[lv] : n.cat[lv];
+      e = pool_in ? cpi::nn_maxpool(in, B, hl(lv), wl(lv), L.cin, n.pool[lv], ws)
+                  : cpi::nn_upcat(low, in, B, hl(lv + 1), wl(lv + 1), c_low, L.cin - c_low,
+                                  n.cat[lv], ws);
+      if (e != hipSuccess) return e;
+      w.low = nullptr;
+      w.c_low = w.pool_in = 0;
+    }
     const bool in1 = i == ENC1A && !gin;
     w.part = n.wpart;
     auto run = [&](int phases) {

@@ -283,6 +283,9 @@ struct NnWgradArgs {
 // dw / db (part set), 3 both (the reduction may go on another stream, after
 // the first phase and before the partial buffer is used again)
 hipError_t nn_conv_wgrad(const NnWgradArgs& a, hipStream_t s, int phases = 3);
+// Whether it takes this shape's input as [upsampled low, in] or pooled; where
+// not (rows of millions of columns), the caller writes that input out first.
+bool nn_conv_wgrad_takes_low(const NnWgradArgs& a);
 // floats of partial sums nn_conv_wgrad uses for this shape (the part buffer)
 int64_t nn_conv_wgrad_part_floats(const NnWgradArgs& a);
 // db[n] += sum over the M pixels of dy[m][n]

@@ -1811,16 +1811,18 @@ int64_t lds_groups(const NnConvArgs& a, int th, int nt) {
 // CU: with it the network took 606 instead of 576 us at batch 64 of 128 x 128
 // and 1107 instead of 1041 us at batch 128.
 int conv3_tile(const NnConvArgs& a) {
-  // (byte offsets within a tile's rows and the weights stay below 2^31)
-  if (a.ks != 3 || a.Cin % 32 != 0 || int64_t(a.W) * a.Cin >= (int64_t(1) << 25) ||
-      int64_t(a.Kpad) * 128 >= (int64_t(1) << 30))
-    return -1;
+  if (a.ks != 3 || a.Cin % 32 != 0 || int64_t(a.Kpad) * 128 >= (int64_t(1) << 30)) return -1;
   for (int64_t kMin = 512; kMin >= 128; kMin /= 2) {
-    if (a.Cout % 64 == 0 && lds_groups(a, 8, 64) >= kMin) return 0;
-    if (a.Cout % 64 == 0 && lds_groups(a, 4, 64) >= kMin) return 1;
-    if (lds_groups(a, 16, 32) >= kMin) return 2;
-    if (lds_groups(a, 8, 32) >= kMin) return 3;
-    if (lds_groups(a, 4, 32) >= kMin) return 4;
+    // (byte offsets within a tile's rows and the weights stay below 2^31)
+    auto takes = [&](int th, int nt) {
+      return a.Cout % nt == 0 && lds_groups(a, th, nt) >= kMin &&
+             int64_t(th + 2) * a.W * a.Cin < (int64_t(1) << 30);
+    };
+    if (takes(8, 64)) return 0;
+    if (takes(4, 64)) return 1;
+    if (takes(16, 32)) return 2;
+    if (takes(8, 32)) return 3;
+    if (takes(4, 32)) return 4;
   }
   return -1;
 }
@@ -1886,12 +1888,12 @@ WgradPlan wgrad_plan(const NnWgradArgs& a) {
   const int NT = wide ? 64 : 32;
   p.gx = unsigned(a.Cout / NT);
   int64_t z;
+  const int tw = a.W >= 64 ? 64 : a.W >= 32 ? 32 : 16;
+  const int rows = (wide ? 128 : 256) / tw;
   // (32-bit block numbers, and byte offsets within a block's rows below 2^31)
-  const int64_t wide_row = int64_t(1) << 25;
-  if (a.ks == 3 && a.Cin % 32 == 0 && int64_t(a.W) * a.Cin < wide_row &&
-      int64_t(a.W) * a.Cout < wide_row && int64_t(a.B) * a.H * a.W < (int64_t(1) << 31)) {
-    const int tw = a.W >= 64 ? 64 : a.W >= 32 ? 32 : 16;
-    const int rows = (wide ? 128 : 256) / tw;
+  if (a.ks == 3 && a.Cin % 32 == 0 && int64_t(rows + 2) * a.W * a.Cin < (int64_t(1) << 30) &&
+      int64_t(rows) * a.W * a.Cout < (int64_t(1) << 30) &&
+      int64_t(a.B) * a.H * a.W < (int64_t(1) << 31)) {
     p.kind = (wide ? 0 : 3) + (tw == 64 ? 0 : tw == 32 ? 1 : 2);
     p.gy = unsigned(a.Cin / 32);
     const int64_t nb = int64_t(a.B) * ((a.H + rows - 1) / rows) * ((a.W + tw - 1) / tw);
@@ -1917,13 +1919,16 @@ int64_t nn_conv_wgrad_part_floats(const NnWgradArgs& a) {
   return int64_t(p.gz) * (int64_t(a.Cout) * a.ks * a.ks * a.Cin + a.Cout);
 }
 
+bool nn_conv_wgrad_takes_low(const NnWgradArgs& a) {
+  if (a.low && (a.pool_in || a.c_low % 32 || a.H % 2 || a.W % 2)) return false;
+  return wgrad_plan(a).kind <= 5;
+}
+
 hipError_t nn_conv_wgrad(const NnWgradArgs& a, hipStream_t s, int phases) {
   if (a.ks != 3 && a.ks != 1) return hipErrorInvalidValue;
   if ((phases & 2) && !(phases & 1) && !a.part) return hipErrorInvalidValue;
   const WgradPlan p = wgrad_plan(a);
-  if ((a.low || a.pool_in) &&
-      (p.kind > 5 || (a.low && a.pool_in) || (a.low && (a.c_low % 32 || a.H % 2 || a.W % 2))))
-    return hipErrorInvalidValue;
+  if ((a.low || a.pool_in) && !nn_conv_wgrad_takes_low(a)) return hipErrorInvalidValue;
   if (a.part && a.part_cap < nn_conv_wgrad_part_floats(a)) return hipErrorInvalidValue;
   const dim3 grid(p.gx, p.gy, p.gz), block(256);
   if (phases & 1) switch (p.kind) {
