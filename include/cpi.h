@@ -216,10 +216,13 @@ cpi_status cpi_refocus_config(const cpi_geometry* g, int32_t n_alpha,
  *     two passes: the column interpolants of every view row, summed over x_b,
  *     are written to the workspace for each (plane, y_b), then the row
  *     weights fold them over y_b.  Lanes are view rows, so column cells and
- *     weights are shared by a wave.  Takes views of at most 256 rows and
- *     plane groups whose sample columns, for the chosen output columns per
- *     work-group, span at most 64 view columns; cpi_refocus uses the
- *     column-sum kernel where it does not apply. */
+ *     weights are shared by a wave.  Takes plane groups whose sample columns,
+ *     for the chosen output columns per work-group, span at most 64 view
+ *     columns.  Where this is the configuration in use, cpi_refocus takes the
+ *     column interpolants from registers, by a split of its own, if every
+ *     view window fits there (the same sums in the same order: bit for bit
+ *     the result of any shape named here); if not, the configured shape or
+ *     the next one that applies; and the column-sum kernel where none does. */
 typedef enum {
   CPI_REFOCUS_ROWS = 0,
   CPI_REFOCUS_COLUMN_SUMS = 1,
@@ -236,9 +239,7 @@ typedef enum {
  * other kernels, and reported as 0 for them).  For CPI_REFOCUS_VIEW_ROWS,
  * rows_per_wave holds the output columns per work-group instead, with
  * (planes, columns) in (8, 8), (4, 16), (8, 16), (16, 16), (8, 32), and
- * view_splits is ignored; plane sets whose view windows fit in registers are
- * split by the library itself, whichever of these is named (the sums and
- * their order are the same). */
+ * view_splits is ignored. */
 typedef struct {
   int32_t planes_per_group;
   int32_t rows_per_wave;

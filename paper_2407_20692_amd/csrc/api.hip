@@ -310,13 +310,14 @@ cpi_status refocus_enqueue(const float* gamma, const cpi_geometry* g, const doub
   }
   RefocusConfig c = forced ? *forced : refocus_config_for(g, n_alpha);
   float* partial = reinterpret_cast<float*>(ws + pl.off_partial);
-  if (c.mode == 2) {
-    // The register-window x pass makes its own split of the work and takes
-    // every plane set whose windows fit it; an explicit configuration also
-    // has to be one that the LDS-tap x pass would take.
+  if (c.mode == 2 || c.mode == kRefModeWindow) {
+    // cpi_refocus takes the register-window x pass for every plane set whose
+    // windows fit it, whatever row-lane shape is configured (the sums and their
+    // order are the same); an explicit shape runs as named.
     WindowSplit sp;
-    const bool window = window_split(rg, alphas, n_alpha, pl.rows_chunk, &sp);
-    bool taps = (!window || forced) &&
+    const bool window = (!forced || c.mode == kRefModeWindow) &&
+                        window_split(rg, alphas, n_alpha, pl.rows_chunk, &sp);
+    bool taps = !window && c.mode == 2 &&
                 rows_supported(rg, alphas, n_alpha, c.kp, c.rw, pl.rows_chunk);
     if (!window && !taps && !forced) {
       // the next LDS-tap shape whose windows hold the plane set, in order of
@@ -330,7 +331,7 @@ cpi_status refocus_enqueue(const float* gamma, const cpi_geometry* g, const doub
           break;
         }
     }
-    if (taps || (window && !forced)) {
+    if (window || taps) {
       RowsWorkspace w;
       w.xe = reinterpret_cast<int32_t*>(ws + pl.off_rows_xe);
       w.yr = reinterpret_cast<int2*>(ws + pl.off_rows_yr);

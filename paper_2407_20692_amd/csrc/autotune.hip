@@ -148,6 +148,10 @@ cpi_status autotune_refocus(const float* gamma, const cpi_geometry* g, const dou
                             hipStream_t st, std::string* why) {
   std::vector<RefocusConfig> cands;
   const int max_splits = g->hb < kMaxViewSplits ? g->hb : kMaxViewSplits;
+  // Row-lane: the register-window x pass, once, where it takes the plane set,
+  // as cpi_refocus then runs it for any row-lane configuration; else the
+  // LDS-tap shapes.
+  cands.push_back(RefocusConfig{8, 32, 1, kRefModeWindow, 2});
   for (const std::pair<int, int>& t : {std::make_pair(8, 8), std::make_pair(4, 16),
                                        std::make_pair(8, 16), std::make_pair(16, 16),
                                        std::make_pair(8, 32)})
@@ -201,11 +205,14 @@ cpi_status autotune_refocus(const float* gamma, const cpi_geometry* g, const dou
   // and four stages.
   std::vector<std::pair<double, RefocusConfig>> sep_times;
   cpi_status fail = CPI_OK;
+  bool window = false;
   for (const RefocusConfig& c : cands) {
     double us;
+    if (c.mode == 2 && window) continue;
     fail = time_of(c, &us);
     if (fail != CPI_OK) break;
     if (us < 0) continue;
+    if (c.mode == kRefModeWindow) window = true;
     if (c.mode == 1) sep_times.push_back({us, c});
     if (us < best_us) {
       best_us = us;
@@ -237,9 +244,11 @@ cpi_status autotune_refocus(const float* gamma, const cpi_geometry* g, const dou
   hipEventDestroy(e0);
   hipEventDestroy(e1);
   {
+    RefocusConfig kept = best;
+    if (kept.mode == kRefModeWindow) kept.mode = 2;
     std::lock_guard<std::mutex> lk(g_mu);
     load_cache_locked();
-    store_cache_locked(shape_key(g, n_alpha), best, best_us);
+    store_cache_locked(shape_key(g, n_alpha), kept, best_us);
   }
   cpi_status s = refocus_enqueue(gamma, g, alphas, n_alpha, out, ws, ws_bytes, st, &best, false);
   if (s != CPI_OK) return s;

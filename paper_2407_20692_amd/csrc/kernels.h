@@ -161,10 +161,14 @@ struct RefocusConfig {
   int splits = 1;    // view-row splits (partial sums reduced afterwards)
   int mode = 0;      // 0: per-row interpolation (k_ref_batched); 1: column sums over x_b
                      // first, row weights once per y_b (k_ref_sep); 2: row-lane x pass
-                     // and fold (k_ref_window or k_ref_rows), with kp planes x rw output columns per
-                     // work-group (splits and stages unused)
+                     // and fold (k_ref_rows), with kp planes x rw output columns per
+                     // work-group (splits and stages unused), which cpi_refocus
+                     // replaces by k_ref_window where the plane set's windows fit that
   int stages = 3;    // mode 1: view windows staged in LDS (2, 3 or 4)
 };
+// Within the library: the register-window x pass as such, which has no other
+// parameters.  No caller names it (refocus_config_supported refuses it).
+constexpr int kRefModeWindow = 3;
 bool refocus_config_supported(const RefocusConfig& c);
 // bounds: workspace for the window bounds per (plane group, tile column,
 // view column) and (plane group, tile row, view row), two ints each; sized

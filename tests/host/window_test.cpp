@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
+#include <cstdlib>
 #include <vector>
 
 #include "refocus_window_plan.h"
@@ -111,7 +112,24 @@ static std::vector<double> clusters(double a, double b, double step, int each) {
   return v;
 }
 
-int main() {
+// The split of one geometry and plane list: wa ha wb hb out_w out_h mag_x mag_y
+// ca_x ca_y cb_x cb_y alpha ..
+static int print_split(int argc, char** argv) {
+  std::vector<double> v;
+  for (int i = 1; i < argc; ++i) v.push_back(std::atof(argv[i]));
+  const RefGeom g{int(v[0]), int(v[1]), int(v[2]), int(v[3]), int(v[4]), int(v[5]),
+                  v[6],      v[7],      v[8],      v[9],      v[10],     v[11]};
+  const std::vector<double> al(v.begin() + 12, v.end());
+  WindowSplit w;
+  if (window_split(g, al.data(), int(al.size()), (int64_t(al.size()) + 15) / 16 * 16, &w))
+    std::printf("%d %d %d %d\n", w.np, w.xc, w.pg, w.blocks);
+  else
+    std::printf("none\n");
+  return 0;
+}
+
+int main(int argc, char** argv) {
+  if (argc > 13) return print_split(argc, argv);
   for (int ha : {2, 3, 8, 15, 16, 17, 31, 33, 47, 63, 64, 65, 100, 128, 200})
     for (int wa : {64, 65, 150, 256}) copies(wa, ha);
   // evenly spaced planes
