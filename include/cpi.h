@@ -160,10 +160,17 @@ cpi_status cpi_correlate_f32_plain(const void* frames_a, const void* frames_b,
  *
  * cpi_refocus runs the batched kernel (many planes per launch) with the tile
  * configuration cached by cpi_autotune_refocus for this shape, or a default.
+ * Without a cached configuration, small stacks (at most 2^24 (plane, output
+ * pixel, view) triples), and those of at most 8 planes and fewer than 2^18
+ * output pixels in all to which no row-lane configuration applies, are summed
+ * by direct gathers in one launch instead (each pixel's views over 16 threads,
+ * sums in double).
  * cpi_refocus_plain runs one plane per launch with direct gathers.
- * cpi_autotune_refocus times the candidate configurations on these inputs,
- * caches the fastest (in memory and, if CPI_AUTOTUNE_CACHE names a file, on
- * disk), synchronises `stream`, and leaves the refocused stack in `out`.
+ * cpi_autotune_refocus times the candidate configurations on these inputs
+ * (and the direct gathers, where cpi_refocus takes them by itself), caches the
+ * fastest (in memory and, if CPI_AUTOTUNE_CACHE names a file, on disk; nothing,
+ * or no longer anything, where the gathers are), synchronises `stream`, and
+ * leaves the refocused stack in `out`.
  * Errors: CPI_ERR_INVALID_ARG (null pointers, non-positive sizes, non-finite
  * geometry or alpha, n_alpha out of range), CPI_ERR_WORKSPACE, CPI_ERR_DEVICE.
  * ------------------------------------------------------------------------- */
@@ -181,6 +188,9 @@ cpi_status cpi_refocus(const float* gamma, const cpi_geometry* g,
  * except that the row-lane kernel is replaced by the column-sum kernel and
  * view-row splits are halved until the tables and partial sums fit the
  * array: the result is that of cpi_refocus_tiled with that configuration.
+ * Without a cached configuration, stacks of the sizes that cpi_refocus sums by
+ * direct gathers are summed so here, also where a row-lane configuration would
+ * apply: bit for bit the result of cpi_refocus where that gathers.
  * Every call on one device shares its array, so calls that overlap on one
  * device (other streams, other threads) race; serialise them.  Nothing in
  * the array needs clearing between calls.
@@ -196,9 +206,9 @@ cpi_status cpi_autotune_refocus(const float* gamma, const cpi_geometry* g,
                                 const double* alphas, int32_t n_alpha, float* out,
                                 void* workspace, size_t workspace_bytes,
                                 void* stream);
-/* The batched-kernel configuration cpi_refocus uses for this shape on the
- * current device: planes per work-group, output rows per wave and view-row
- * splits (host pointers). */
+/* The batched-kernel configuration of cpi_refocus for this shape on the
+ * current device (of stacks that it does not sum by direct gathers): planes per
+ * work-group, output rows per wave and view-row splits (host pointers). */
 cpi_status cpi_refocus_config(const cpi_geometry* g, int32_t n_alpha,
                               int32_t* planes_per_group, int32_t* rows_per_wave,
                               int32_t* view_splits);
@@ -248,8 +258,9 @@ typedef struct {
   int32_t stages;
 } cpi_refocus_tiles;
 
-/* The configuration cpi_refocus uses for this shape on the current device
- * (cached by cpi_autotune_refocus, or the default).  `out` is a host pointer. */
+/* The batched-kernel configuration of cpi_refocus for this shape on the current
+ * device (cached by cpi_autotune_refocus, or the default, which is not used for
+ * stacks that cpi_refocus sums by direct gathers).  `out` is a host pointer. */
 cpi_status cpi_refocus_get_tiles(const cpi_geometry* g, int32_t n_alpha,
                                  cpi_refocus_tiles* out);
 /* cpi_refocus with an explicit configuration `tiles` (host pointer) instead

@@ -279,6 +279,24 @@ cpi_status enqueue_tables(const cpi_geometry* g, const double* alphas, int32_t n
   return CPI_OK;
 }
 
+// Row-lane shapes with LDS taps, in order of pairs per work-group.
+constexpr std::pair<int, int> kRowShapes[] = {{8, 32}, {16, 16}, {8, 16}, {16, 8}, {8, 8}, {4, 16}};
+
+// Whether cpi_refocus takes an untuned stack by direct gathers: small ones, and
+// those of few planes that would go to the column-sum kernel.
+bool default_gathers(const cpi_geometry* g, const double* alphas, int32_t n_alpha,
+                     const cpi::RefocusPlan& pl) {
+  const cpi::RefGeom rg = ref_geom(g);
+  if (cpi::refocus_gather_fits(rg, n_alpha, false)) return true;
+  if (!cpi::refocus_gather_fits(rg, n_alpha, true)) return false;
+  if (cpi::default_refocus_config(g, n_alpha).mode != 2) return true;
+  cpi::WindowSplit sp;
+  if (cpi::window_split(rg, alphas, n_alpha, pl.rows_chunk, &sp)) return false;
+  for (const auto& t : kRowShapes)
+    if (cpi::rows_supported(rg, alphas, n_alpha, t.first, t.second, pl.rows_chunk)) return false;
+  return true;
+}
+
 }  // namespace
 
 namespace cpi {
@@ -292,7 +310,17 @@ cpi_status refocus_enqueue(const float* gamma, const cpi_geometry* g, const doub
   if (s != CPI_OK) return s;
   uint8_t* ws = static_cast<uint8_t*>(workspace);
   const RefGeom rg = ref_geom(g);
-  const bool gather = !plain && !forced && refocus_gather_fits(rg, n_alpha, false);
+  RefocusConfig c;
+  bool tuned = false;
+  if (forced)
+    c = *forced;
+  else if (!plain)
+    c = refocus_config_for(g, n_alpha, &tuned);
+  // (a tuned configuration, timed against the gathers, is used as it is)
+  const bool gather = !plain && (forced ? c.mode == kRefModeGather
+                                        : !tuned && refocus_gather_fits(rg, n_alpha, false));
+  if (forced && gather && !default_gathers(g, alphas, n_alpha, pl))
+    return set_error(CPI_ERR_UNSUPPORTED, "the gathers do not take this stack");
   s = enqueue_tables(g, alphas, n_alpha, pl, ws, st, !gather);
   if (s != CPI_OK) return s;
   const int32_t* itab = reinterpret_cast<const int32_t*>(ws + pl.off_itab);
@@ -308,7 +336,6 @@ cpi_status refocus_enqueue(const float* gamma, const cpi_geometry* g, const doub
       CPI_HIP(refocus_plain(gamma, rg, itab, ftab, pl.table_stride, k, out, st), "refocus");
     return CPI_OK;
   }
-  RefocusConfig c = forced ? *forced : refocus_config_for(g, n_alpha);
   float* partial = reinterpret_cast<float*>(ws + pl.off_partial);
   if (c.mode == 2 || c.mode == kRefModeWindow) {
     // cpi_refocus takes the register-window x pass for every plane set whose
@@ -320,10 +347,8 @@ cpi_status refocus_enqueue(const float* gamma, const cpi_geometry* g, const doub
     bool taps = !window && c.mode == 2 &&
                 rows_supported(rg, alphas, n_alpha, c.kp, c.rw, pl.rows_chunk);
     if (!window && !taps && !forced) {
-      // the next LDS-tap shape whose windows hold the plane set, in order of
-      // pairs per work-group
-      for (const auto& t : {std::make_pair(8, 32), std::make_pair(16, 16), std::make_pair(8, 16),
-                            std::make_pair(16, 8), std::make_pair(8, 8), std::make_pair(4, 16)})
+      // the next LDS-tap shape whose windows hold the plane set
+      for (const auto& t : kRowShapes)
         if (rows_supported(rg, alphas, n_alpha, t.first, t.second, pl.rows_chunk)) {
           c.kp = t.first;
           c.rw = t.second;
@@ -351,7 +376,7 @@ cpi_status refocus_enqueue(const float* gamma, const cpi_geometry* g, const doub
                        "row-lane refocus does not take this geometry or plane set");
     c = default_sep_config(g, n_alpha);
   }
-  if (!forced && refocus_gather_fits(rg, n_alpha, true)) {
+  if (!forced && !tuned && refocus_gather_fits(rg, n_alpha, true)) {
     ProfScope ps("refocus_batched", st);
     CPI_HIP(refocus_gather(gamma, rg, itab, ftab, pl.table_stride, n_alpha, out, st), "refocus");
     return CPI_OK;
@@ -366,10 +391,11 @@ cpi_status refocus_enqueue(const float* gamma, const cpi_geometry* g, const doub
 // Enqueue with an explicit batched configuration against a workspace of
 // `ws_bytes`, which must hold the tables and that configuration's partial
 // sums (not the whole cpi_refocus_workspace_size).  Column-sum and per-row
-// kernels only.
+// kernels only, or with `gather` direct gathers where refocus_enqueue would
+// take those instead.
 cpi_status refocus_enqueue_config(const float* gamma, const cpi_geometry* g, const double* alphas,
                                   int32_t n_alpha, float* out, void* workspace, size_t ws_bytes,
-                                  hipStream_t st, const RefocusConfig& c) {
+                                  hipStream_t st, const RefocusConfig& c, bool gather) {
   RefocusPlan pl;
   std::string why;
   cpi_status s = plan_refocus(g, n_alpha, &pl, &why);
@@ -390,7 +416,7 @@ cpi_status refocus_enqueue_config(const float* gamma, const cpi_geometry* g, con
                                             std::to_string(need) + " bytes");
   uint8_t* ws = static_cast<uint8_t*>(workspace);
   const RefGeom rg = ref_geom(g);
-  const bool gather = refocus_gather_fits(rg, n_alpha, true);   // as refocus_enqueue takes it
+  gather = gather && refocus_gather_fits(rg, n_alpha, true);
   s = enqueue_tables(g, alphas, n_alpha, pl, ws, st, !gather);
   if (s != CPI_OK) return s;
   const int32_t* itab = reinterpret_cast<const int32_t*>(ws + pl.off_itab);
@@ -746,7 +772,8 @@ cpi_status cpi_refocus_noalloc(const float* gamma, const cpi_geometry* g, const 
     // The configuration cpi_refocus would take, restricted to the kernels
     // whose workspace is the tables plus split partial sums, with view-row
     // splits halved until that fits the scratch array.
-    cpi::RefocusConfig c = cpi::refocus_config_for(g, n_alpha);
+    bool tuned = false;
+    cpi::RefocusConfig c = cpi::refocus_config_for(g, n_alpha, &tuned);
     if (c.mode == 2) c = cpi::default_sep_config(g, n_alpha);
     auto need = [&](const cpi::RefocusConfig& k) {
       const int sp = std::min<int>(k.splits, g->hb);
@@ -764,7 +791,7 @@ cpi_status cpi_refocus_noalloc(const float* gamma, const cpi_geometry* g, const 
     s = noalloc_scratch(&ws);
     if (s != CPI_OK) return s;
     return cpi::refocus_enqueue_config(gamma, g, alphas, n_alpha, out, ws, need(c),
-                                       static_cast<hipStream_t>(stream), c);
+                                       static_cast<hipStream_t>(stream), c, !tuned);
   });
 }
 

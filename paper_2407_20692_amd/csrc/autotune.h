@@ -11,8 +11,8 @@
 namespace cpi {
 
 // Configuration used by cpi_refocus: the cached autotuned one for this shape
-// and device if any, else a default sized to fill the device.
-RefocusConfig refocus_config_for(const cpi_geometry* g, int32_t n_alpha);
+// and device if any (*tuned), else a default sized to fill the device.
+RefocusConfig refocus_config_for(const cpi_geometry* g, int32_t n_alpha, bool* tuned = nullptr);
 RefocusConfig default_refocus_config(const cpi_geometry* g, int32_t n_alpha);
 // The column-sum kernel's default, taken where the row-lane kernel does not
 // run the geometry or plane set.
@@ -24,14 +24,15 @@ cpi_status autotune_refocus(const float* gamma, const cpi_geometry* g, const dou
                             int32_t n_alpha, float* out, void* ws, size_t ws_bytes,
                             hipStream_t st, std::string* why);
 
-// Enqueue a refocus (defined with the C ABI): `forced` overrides the
-// configuration; `plain` selects the one-plane-per-launch kernel.
 // Enqueue with an explicit column-sum or per-row configuration against a
-// workspace that holds the tables and that configuration's partial sums only.
+// workspace that holds the tables and that configuration's partial sums only;
+// `gather`: by direct gathers instead, where they take the stack.
 cpi_status refocus_enqueue_config(const float* gamma, const cpi_geometry* g, const double* alphas,
                                   int32_t n_alpha, float* out, void* workspace, size_t ws_bytes,
-                                  hipStream_t st, const RefocusConfig& c);
+                                  hipStream_t st, const RefocusConfig& c, bool gather);
 
+// Enqueue a refocus (defined with the C ABI): `forced` overrides the
+// configuration; `plain` selects the one-plane-per-launch kernel.
 cpi_status refocus_enqueue(const float* gamma, const cpi_geometry* g, const double* alphas,
                            int32_t n_alpha, float* out, void* workspace, size_t ws_bytes,
                            hipStream_t st, const RefocusConfig* forced, bool plain);

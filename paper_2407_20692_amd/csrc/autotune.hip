@@ -4,7 +4,9 @@
 // work-group, view-row splits, staged windows) are chosen by timing the
 // candidates on the caller's inputs.  Results are kept
 // per (shape, device) in memory and, when CPI_AUTOTUNE_CACHE names a file, in
-// a text cache of lines "key kp rw splits kernel stages microseconds".
+// a text cache of lines "key kp rw splits kernel stages microseconds"; a line
+// "#default key" takes back earlier ones of that shape, for which the library's own
+// choice (direct gathers) turned out the fastest.
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -46,11 +48,15 @@ std::string device_tag() {
   return s;
 }
 
+std::string shape_name(const cpi_geometry* g, int32_t n_alpha) {
+  char name[128];
+  std::snprintf(name, sizeof(name), "wa%d_ha%d_wb%d_hb%d_ow%d_oh%d_na%d@", int(g->wa), int(g->ha),
+                int(g->wb), int(g->hb), int(g->out_w), int(g->out_h), int(n_alpha));
+  return name;
+}
+
 std::string shape_key(const cpi_geometry* g, int32_t n_alpha) {
-  std::ostringstream os;
-  os << "wa" << g->wa << "_ha" << g->ha << "_wb" << g->wb << "_hb" << g->hb << "_ow" << g->out_w
-     << "_oh" << g->out_h << "_na" << n_alpha << "@" << device_tag();
-  return os.str();
+  return shape_name(g, n_alpha) + device_tag();
 }
 
 // Loads the cache file once; a malformed file is ignored as a whole.
@@ -64,6 +70,7 @@ void load_cache_locked() {
   std::map<std::string, RefocusConfig> tmp;
   std::string line;
   while (std::getline(f, line)) {
+    if (line.compare(0, 9, "#default ") == 0) tmp.erase(line.substr(9));
     if (line.empty() || line[0] == '#') continue;
     std::istringstream is(line);
     std::string key;
@@ -88,6 +95,15 @@ void store_cache_locked(const std::string& key, const RefocusConfig& c, double u
   if (f)
     f << key << ' ' << c.kp << ' ' << c.rw << ' ' << c.splits << ' ' << c.mode << ' '
       << c.stages << ' ' << us << '\n';
+}
+
+// The shape goes back to the library's own choice.
+void drop_cache_locked(const std::string& key) {
+  if (g_cache.erase(key) == 0) return;
+  const char* path = std::getenv("CPI_AUTOTUNE_CACHE");
+  if (!path || !*path) return;
+  std::ofstream f(path, std::ios::app);
+  if (f) f << "#default " << key << '\n';
 }
 
 int64_t workgroups(const cpi_geometry* g, int32_t n_alpha, const RefocusConfig& c) {
@@ -129,12 +145,24 @@ RefocusConfig default_refocus_config(const cpi_geometry* g, int32_t n_alpha) {
   return c;
 }
 
-RefocusConfig refocus_config_for(const cpi_geometry* g, int32_t n_alpha) {
-  const std::string key = shape_key(g, n_alpha);
+RefocusConfig refocus_config_for(const cpi_geometry* g, int32_t n_alpha, bool* tuned) {
+  if (tuned) *tuned = false;
+  std::string shape;
+  {
+    // (the device is asked for only if some device's entry has this shape)
+    std::lock_guard<std::mutex> lk(g_mu);
+    load_cache_locked();
+    if (g_cache.empty()) return default_refocus_config(g, n_alpha);
+    shape = shape_name(g, n_alpha);
+    const auto it = g_cache.lower_bound(shape);
+    if (it == g_cache.end() || it->first.compare(0, shape.size(), shape) != 0)
+      return default_refocus_config(g, n_alpha);
+  }
+  const std::string key = shape + device_tag();
   std::lock_guard<std::mutex> lk(g_mu);
-  load_cache_locked();
   auto it = g_cache.find(key);
   if (it != g_cache.end()) {
+    if (tuned) *tuned = true;
     RefocusConfig c = it->second;
     const int max_splits = g->hb < kMaxViewSplits ? g->hb : kMaxViewSplits;
     if (c.splits > max_splits) c.splits = max_splits;
@@ -148,6 +176,8 @@ cpi_status autotune_refocus(const float* gamma, const cpi_geometry* g, const dou
                             hipStream_t st, std::string* why) {
   std::vector<RefocusConfig> cands;
   const int max_splits = g->hb < kMaxViewSplits ? g->hb : kMaxViewSplits;
+  // The direct gathers, where cpi_refocus takes the stack so by itself.
+  cands.push_back(RefocusConfig{1, 8, 1, kRefModeGather, 2});
   // Row-lane: the register-window x pass, once, where it takes the plane set,
   // as cpi_refocus then runs it for any row-lane configuration; else the
   // LDS-tap shapes.
@@ -246,9 +276,13 @@ cpi_status autotune_refocus(const float* gamma, const cpi_geometry* g, const dou
   {
     RefocusConfig kept = best;
     if (kept.mode == kRefModeWindow) kept.mode = 2;
+    const std::string key = shape_key(g, n_alpha);
     std::lock_guard<std::mutex> lk(g_mu);
     load_cache_locked();
-    store_cache_locked(shape_key(g, n_alpha), kept, best_us);
+    if (kept.mode == kRefModeGather)
+      drop_cache_locked(key);
+    else
+      store_cache_locked(key, kept, best_us);
   }
   cpi_status s = refocus_enqueue(gamma, g, alphas, n_alpha, out, ws, ws_bytes, st, &best, false);
   if (s != CPI_OK) return s;

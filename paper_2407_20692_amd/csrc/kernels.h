@@ -166,9 +166,10 @@ struct RefocusConfig {
                      // replaces by k_ref_window where the plane set's windows fit that
   int stages = 3;    // mode 1: view windows staged in LDS (2, 3 or 4)
 };
-// Within the library: the register-window x pass as such, which has no other
-// parameters.  No caller names it (refocus_config_supported refuses it).
-constexpr int kRefModeWindow = 3;
+// Within the library: the register-window x pass and the direct gathers as such,
+// which have no other parameters.  No caller names them
+// (refocus_config_supported refuses them).
+constexpr int kRefModeWindow = 3, kRefModeGather = 4;
 bool refocus_config_supported(const RefocusConfig& c);
 // bounds: workspace for the window bounds per (plane group, tile column,
 // view column) and (plane group, tile row, view row), two ints each; sized
