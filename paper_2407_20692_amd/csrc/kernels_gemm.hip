@@ -681,7 +681,11 @@ __device__ __forceinline__ void lds_read_frags(uint32_t a, uint32_t b, v4i (&x)[
 // fragments (xn, yn) from LDS are issued ahead of this step's matrix ops on
 // (x, y) and waited for behind them.  All waves of a work-group run in step, so
 // a read that is waited for before its own matrix ops leaves the matrix cores
-// idle meanwhile.
+// idle meanwhile.  The last sums are still being written when the block ends:
+// between two blocks nothing but matrix ops may touch them, which the compiler
+// does not know and test_host_mfma_wait checks in its output.  (Waiting inside the
+// block, 11 states, took a call on 20000 frames of counts, Da 128 x 128, Db
+// 64 x 64, from 1539 to 1563 us.)
 __device__ __forceinline__ void bytes_step(uint32_t a, uint32_t b, const v4i (&x)[8],
                                            const v4i (&y)[4], v4i (&xn)[8], v4i (&yn)[4],
                                            v4i (&acc)[8][4]) {
@@ -980,7 +984,7 @@ __device__ __forceinline__ void gemm_bytes_big(const GemmArgs& g, uint8_t* stage
   }
   if (g.kblocks & 1)   // (reads x1, y1 once more, not used)
     bytes_step(ra, rb, x0, y0, x1, y1, acc);
-  // (the sums are read by ordinary instructions from here on)
+  // (the sums are read by ordinary instructions from here on, no earlier)
   asm volatile("s_nop 15\ns_nop 15" ::: "memory");
   __syncthreads();
   bytes_epilogue<MODE, FM, FN, WM, WN, 2 * kBigStage>(g, stage, acc, mb, nb, offset);

@@ -206,8 +206,7 @@ typedef int nn_i4 __attribute__((ext_vector_type(4)));
 
 // LDS-direct copy of 16 bytes per lane to 1 KB from dst; an offset at or above
 // 2^31 delivers zeros.  (Assembly: for the builtin the compiler waits for all
-// copies before transposing reads of the same array.  Nothing else in these
-// kernels uses M0.)
+// copies before transposing reads of the same array.)
 __device__ __forceinline__ void copy_lds16(nn_i4 from, uint8_t* dst, uint32_t voff,
                                            uint32_t soff) {
   asm volatile(
@@ -215,7 +214,7 @@ __device__ __forceinline__ void copy_lds16(nn_i4 from, uint8_t* dst, uint32_t vo
       "s_nop 4\n"
       "buffer_load_dwordx4 %1, %2, %3 offen lds\n" ::"s"(uint32_t(reinterpret_cast<uintptr_t>(dst))),
       "v"(voff), "s"(from), "s"(soff)
-      : "memory");
+      : "m0", "memory");
 }
 __device__ __forceinline__ nn_i4 buffer_at(const void* p) {
   const uint64_t a = reinterpret_cast<uint64_t>(p);

@@ -168,7 +168,7 @@ __global__ __launch_bounds__(256) void k_window_xtab(GeomI g, const int32_t* __r
 // later view into the LDS space of the one before (a second barrier before
 // them where there is only one space), and the multiply-adds.  The cells come
 // through the scalar cache meanwhile, the next view's last words during the
-// multiply-adds.  (M0 is not restored: nothing else in the kernel uses it.)
+// multiply-adds.
 
 // waits until at most n copies of this wave are in flight: ever fewer, until
 // n allows as many
@@ -350,7 +350,7 @@ __global__ __launch_bounds__(256) void k_window_xtab(GeomI g, const int32_t* __r
       "v216", "v217", "v218", "v219", "v220", "v221", "v222", "v223", "v224", "v225", "v226", \
       "v227", "v228", "v229", "v230", "v231", "v232", "v233", "v234", "v235", "v236", "v237", \
       "v238", "v239", "v240", "v241", "v242", "v243", "v244", "v245", "v246", "v247", "v248", \
-      "v249", "v250", "v251", "v252", "v253", "v254", "v255", "scc", "memory"
+      "v249", "v250", "v251", "v252", "v253", "v254", "v255", "m0", "scc", "memory"
 
 typedef int i4v __attribute__((ext_vector_type(4)));
 typedef int i8v __attribute__((ext_vector_type(8)));
@@ -453,7 +453,7 @@ __global__ __launch_bounds__(64 * kWinWaves, 2) void k_ref_window(
                      [rs] "s"(rs), [from] "v"(from), [from1] "v"(from1),
                      [td] "s"(tab0 + uint32_t(k * kWinTabBytes)), [tl] "v"(tl),
                      [tp] "s"(tp + kk * kStep)
-                   : "scc", "memory");
+                   : "m0", "scc", "memory");
       f1 = 2 * nb + 1;
       if (k < last) view += pa;
     }
