@@ -164,7 +164,7 @@ cpi_status cpi_correlate_f32_plain(const void* frames_a, const void* frames_b,
  * pixel, view) triples), and those of at most 8 planes and fewer than 2^18
  * output pixels in all to which no row-lane configuration applies, are summed
  * by direct gathers in one launch instead (each pixel's views over 16 threads,
- * sums in double).
+ * sums in double) where an estimate from the sizes and planes favours that.
  * cpi_refocus_plain runs one plane per launch with direct gathers.
  * cpi_autotune_refocus times the candidate configurations on these inputs
  * (and the direct gathers, where cpi_refocus takes them by itself), caches the
@@ -188,9 +188,9 @@ cpi_status cpi_refocus(const float* gamma, const cpi_geometry* g,
  * except that the row-lane kernel is replaced by the column-sum kernel and
  * view-row splits are halved until the tables and partial sums fit the
  * array: the result is that of cpi_refocus_tiled with that configuration.
- * Without a cached configuration, stacks of the sizes that cpi_refocus sums by
- * direct gathers are summed so here, also where a row-lane configuration would
- * apply: bit for bit the result of cpi_refocus where that gathers.
+ * Without a cached configuration, stacks are summed by direct gathers here by
+ * the rule of cpi_refocus, against that column-sum configuration: where that is
+ * cpi_refocus's own too, the results are equal bit for bit.
  * Every call on one device shares its array, so calls that overlap on one
  * device (other streams, other threads) race; serialise them.  Nothing in
  * the array needs clearing between calls.

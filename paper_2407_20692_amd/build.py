@@ -22,6 +22,7 @@ ARCH = "gfx950"
 SOURCES = [
     "plan.cpp",
     "refocus_window_plan.cpp",
+    "refocus_route.cpp",
     "kernels_ingest.hip",
     "kernels_gemm.hip",
     "kernels_f32.hip",

@@ -21,6 +21,7 @@
 #include "errors.h"
 #include "kernels.h"
 #include "plan.h"
+#include "refocus_route.h"
 
 namespace {
 
@@ -282,19 +283,37 @@ cpi_status enqueue_tables(const cpi_geometry* g, const double* alphas, int32_t n
 // Row-lane shapes with LDS taps, in order of pairs per work-group.
 constexpr std::pair<int, int> kRowShapes[] = {{8, 32}, {16, 16}, {8, 16}, {16, 8}, {8, 8}, {4, 16}};
 
-// Whether cpi_refocus takes an untuned stack by direct gathers: small ones, and
-// those of few planes that would go to the column-sum kernel.
+// The register-window x pass's split of a stack, found at most once per call.
+struct WindowPlan {
+  bool known = false, takes = false;
+  cpi::WindowSplit split;
+  bool find(const cpi::RefGeom& rg, const double* alphas, int32_t n_alpha,
+            const cpi::RefocusPlan& pl) {
+    if (!known) takes = cpi::window_split(rg, alphas, n_alpha, pl.rows_chunk, &split);
+    known = true;
+    return takes;
+  }
+};
+
+// Whether a stack whose configuration would be c goes by direct gathers instead
+// when it is not tuned: small ones, and those of few planes that would go to the
+// column-sum kernel, where the gathers are estimated to be faster.
 bool default_gathers(const cpi_geometry* g, const double* alphas, int32_t n_alpha,
-                     const cpi::RefocusPlan& pl) {
+                     const cpi::RefocusPlan& pl, const cpi::RefocusConfig& c, WindowPlan* wp) {
   const cpi::RefGeom rg = ref_geom(g);
-  if (cpi::refocus_gather_fits(rg, n_alpha, false)) return true;
-  if (!cpi::refocus_gather_fits(rg, n_alpha, true)) return false;
-  if (cpi::default_refocus_config(g, n_alpha).mode != 2) return true;
-  cpi::WindowSplit sp;
-  if (cpi::window_split(rg, alphas, n_alpha, pl.rows_chunk, &sp)) return false;
+  if (!cpi::refocus_gather_takes(rg, n_alpha)) return false;
+  if (cpi::refocus_gather_surely(rg, n_alpha)) return true;
+  const cpi::RefocusConfig sep = c.mode == 1 ? c : cpi::default_sep_config(g, n_alpha);
+  const bool sums = cpi::refocus_gather_wins(rg, alphas, n_alpha, {false, sep.rw, sep.splits});
+  if (c.mode != 2) return sums;
+  const bool lanes = cpi::refocus_gather_wins(rg, alphas, n_alpha, {true});
+  if (sums == lanes) return sums;
+  // (it depends on which would be taken)
+  bool row_lane = wp->find(rg, alphas, n_alpha, pl);
   for (const auto& t : kRowShapes)
-    if (cpi::rows_supported(rg, alphas, n_alpha, t.first, t.second, pl.rows_chunk)) return false;
-  return true;
+    row_lane = row_lane ||
+               cpi::rows_supported(rg, alphas, n_alpha, t.first, t.second, pl.rows_chunk);
+  return row_lane ? lanes : sums;
 }
 
 }  // namespace
@@ -317,9 +336,12 @@ cpi_status refocus_enqueue(const float* gamma, const cpi_geometry* g, const doub
   else if (!plain)
     c = refocus_config_for(g, n_alpha, &tuned);
   // (a tuned configuration, timed against the gathers, is used as it is)
-  const bool gather = !plain && (forced ? c.mode == kRefModeGather
-                                        : !tuned && refocus_gather_fits(rg, n_alpha, false));
-  if (forced && gather && !default_gathers(g, alphas, n_alpha, pl))
+  WindowPlan wp;
+  const bool gather =
+      !plain && (forced ? c.mode == kRefModeGather
+                        : !tuned && default_gathers(g, alphas, n_alpha, pl, c, &wp));
+  if (forced && gather &&
+      !default_gathers(g, alphas, n_alpha, pl, default_refocus_config(g, n_alpha), &wp))
     return set_error(CPI_ERR_UNSUPPORTED, "the gathers do not take this stack");
   s = enqueue_tables(g, alphas, n_alpha, pl, ws, st, !gather);
   if (s != CPI_OK) return s;
@@ -341,9 +363,8 @@ cpi_status refocus_enqueue(const float* gamma, const cpi_geometry* g, const doub
     // cpi_refocus takes the register-window x pass for every plane set whose
     // windows fit it, whatever row-lane shape is configured (the sums and their
     // order are the same); an explicit shape runs as named.
-    WindowSplit sp;
-    const bool window = (!forced || c.mode == kRefModeWindow) &&
-                        window_split(rg, alphas, n_alpha, pl.rows_chunk, &sp);
+    const bool window =
+        (!forced || c.mode == kRefModeWindow) && wp.find(rg, alphas, n_alpha, pl);
     bool taps = !window && c.mode == 2 &&
                 rows_supported(rg, alphas, n_alpha, c.kp, c.rw, pl.rows_chunk);
     if (!window && !taps && !forced) {
@@ -364,7 +385,7 @@ cpi_status refocus_enqueue(const float* gamma, const cpi_geometry* g, const doub
       w.chunk = int(pl.rows_chunk);
       w.wout_cap = pl.rows_wout_cap;
       ProfScope ps("refocus_batched", st);
-      CPI_HIP(window ? refocus_window(gamma, rg, alphas, sp, itab, ftab, ws + pl.off_ytab,
+      CPI_HIP(window ? refocus_window(gamma, rg, alphas, wp.split, itab, ftab, ws + pl.off_ytab,
                                       pl.table_stride, n_alpha, w, out, st)
                      : refocus_rows(gamma, rg, alphas, itab, ftab, ws + pl.off_ytab,
                                     pl.table_stride, n_alpha, c.kp, c.rw, w, out, st),
@@ -376,11 +397,6 @@ cpi_status refocus_enqueue(const float* gamma, const cpi_geometry* g, const doub
                        "row-lane refocus does not take this geometry or plane set");
     c = default_sep_config(g, n_alpha);
   }
-  if (!forced && !tuned && refocus_gather_fits(rg, n_alpha, true)) {
-    ProfScope ps("refocus_batched", st);
-    CPI_HIP(refocus_gather(gamma, rg, itab, ftab, pl.table_stride, n_alpha, out, st), "refocus");
-    return CPI_OK;
-  }
   ProfScope ps("refocus_batched", st);
   CPI_HIP(refocus_batched(gamma, rg, itab, ftab, ws + pl.off_ytab, ws + pl.off_bounds,
                           pl.table_stride, n_alpha, c, partial, out, st),
@@ -391,11 +407,12 @@ cpi_status refocus_enqueue(const float* gamma, const cpi_geometry* g, const doub
 // Enqueue with an explicit batched configuration against a workspace of
 // `ws_bytes`, which must hold the tables and that configuration's partial
 // sums (not the whole cpi_refocus_workspace_size).  Column-sum and per-row
-// kernels only, or with `gather` direct gathers where refocus_enqueue would
-// take those instead.
+// kernels only, or with `gather_for` direct gathers where refocus_enqueue would
+// take those in place of that configuration.
 cpi_status refocus_enqueue_config(const float* gamma, const cpi_geometry* g, const double* alphas,
                                   int32_t n_alpha, float* out, void* workspace, size_t ws_bytes,
-                                  hipStream_t st, const RefocusConfig& c, bool gather) {
+                                  hipStream_t st, const RefocusConfig& c,
+                                  const RefocusConfig* gather_for) {
   RefocusPlan pl;
   std::string why;
   cpi_status s = plan_refocus(g, n_alpha, &pl, &why);
@@ -416,7 +433,8 @@ cpi_status refocus_enqueue_config(const float* gamma, const cpi_geometry* g, con
                                             std::to_string(need) + " bytes");
   uint8_t* ws = static_cast<uint8_t*>(workspace);
   const RefGeom rg = ref_geom(g);
-  gather = gather && refocus_gather_fits(rg, n_alpha, true);
+  WindowPlan wp;
+  const bool gather = gather_for && default_gathers(g, alphas, n_alpha, pl, *gather_for, &wp);
   s = enqueue_tables(g, alphas, n_alpha, pl, ws, st, !gather);
   if (s != CPI_OK) return s;
   const int32_t* itab = reinterpret_cast<const int32_t*>(ws + pl.off_itab);
@@ -775,6 +793,7 @@ cpi_status cpi_refocus_noalloc(const float* gamma, const cpi_geometry* g, const 
     bool tuned = false;
     cpi::RefocusConfig c = cpi::refocus_config_for(g, n_alpha, &tuned);
     if (c.mode == 2) c = cpi::default_sep_config(g, n_alpha);
+    const cpi::RefocusConfig whole = c;
     auto need = [&](const cpi::RefocusConfig& k) {
       const int sp = std::min<int>(k.splits, g->hb);
       return pl.off_partial + (sp > 1 ? size_t(sp) * size_t(n_alpha) * size_t(g->out_w) *
@@ -791,7 +810,8 @@ cpi_status cpi_refocus_noalloc(const float* gamma, const cpi_geometry* g, const 
     s = noalloc_scratch(&ws);
     if (s != CPI_OK) return s;
     return cpi::refocus_enqueue_config(gamma, g, alphas, n_alpha, out, ws, need(c),
-                                       static_cast<hipStream_t>(stream), c, !tuned);
+                                       static_cast<hipStream_t>(stream), c,
+                                       tuned ? nullptr : &whole);
   });
 }
 

@@ -26,10 +26,12 @@ cpi_status autotune_refocus(const float* gamma, const cpi_geometry* g, const dou
 
 // Enqueue with an explicit column-sum or per-row configuration against a
 // workspace that holds the tables and that configuration's partial sums only;
-// `gather`: by direct gathers instead, where they take the stack.
+// `gather_for`: by direct gathers where cpi_refocus would take those in place of
+// that configuration.
 cpi_status refocus_enqueue_config(const float* gamma, const cpi_geometry* g, const double* alphas,
                                   int32_t n_alpha, float* out, void* workspace, size_t ws_bytes,
-                                  hipStream_t st, const RefocusConfig& c, bool gather);
+                                  hipStream_t st, const RefocusConfig& c,
+                                  const RefocusConfig* gather_for);
 
 // Enqueue a refocus (defined with the C ABI): `forced` overrides the
 // configuration; `plain` selects the one-plane-per-launch kernel.

@@ -146,8 +146,7 @@ hipError_t sgemm_gamma(const float* fb, const float* fa, int64_t kpad, int64_t p
 hipError_t refocus_tables(const RefGeom& g, const double* alphas, int first, int count,
                           int64_t stride, int32_t* itab, float* ftab, void* ytab, hipStream_t s);
 // Stacks in one launch after the coordinate tables (the row tables are not
-// needed).  batched: otherwise the batched kernels would take it.
-bool refocus_gather_fits(const RefGeom& g, int n_alpha, bool batched);
+// needed).
 hipError_t refocus_gather(const float* gamma, const RefGeom& g, const int32_t* itab,
                           const float* ftab, int64_t stride, int n_alpha, float* out,
                           hipStream_t s);

@@ -3,6 +3,7 @@
 
 #include "kernels.h"
 #include "refocus_common.h"
+#include "refocus_route.h"
 
 namespace cpi {
 
@@ -15,22 +16,7 @@ namespace {
 // plane; thread (slice, pixel) sums the views slice, slice + 16, ..., and the
 // slices are added in order, in double (in float the sums, longer than the
 // batched kernels', had up to twice their error).  Cells outside a view contribute nothing.
-// Whole calls, batched or row-lane / this, us, at (plane, output pixel, view)
-// triples: Da 32 x 32, Db 16 x 16, 5 planes (1.3e6) 34 / 17, 32 planes (8.4e6)
-// 36 / 24, 64 planes (1.7e7) 39 / 38; Da 64 x 64, Db 16 x 16, 16 planes (1.7e7)
-// 46 / 39; from 3.4e7 on the others win (64 x 64, 32 planes: 48 / 62).
-constexpr int64_t kGatherWork = int64_t(1) << 24;   // triples up to which a stack is taken
-// Planes up to which a stack of any size is taken where otherwise the
-// column-sum kernel would be, whose cost hardly falls with fewer planes.
-// Column-sum / this, us: Da 128 x 128, Db 64 x 64, alpha 0.5 to 1.5, 2 planes
-// 1421 / 288, 8 planes 1383 / 906; Da 150 x 233, Db 100 x 128, 6 planes 12386 / 7361;
-// Da 48 x 48, Db 48 x 48, 8 planes 164 / 118, 16 planes 165 / 184.  And output
-// pixels of all planes, below which they do not fill its work-groups: Da
-// 256 x 256, Db 64 x 64, 4 planes (2^18) 2141 / 1998, Db 8 x 8, 8 planes 64 / 86.
-constexpr int kGatherPlanes = 8;
-constexpr int64_t kGatherOut = int64_t(1) << 18;
-constexpr int kGatherViews = 1024;                  // lens-plane columns and rows in LDS
-
+// (refocus_route.cpp says which stacks are taken and what they cost.)
 __global__ __launch_bounds__(256) void k_ref_gather(const float* __restrict__ gamma, GeomI g,
                                                     const int32_t* __restrict__ itab,
                                                     const float* __restrict__ ftab,
@@ -99,18 +85,10 @@ __global__ __launch_bounds__(256) void k_ref_gather(const float* __restrict__ ga
 
 }  // namespace
 
-bool refocus_gather_fits(const RefGeom& g, int n_alpha, bool batched) {
-  const int64_t opix = int64_t(g.out_w) * g.out_h;
-  return g.wa >= 2 && g.ha >= 2 && int64_t(g.wb) + g.hb <= kGatherViews && n_alpha <= 65535 &&
-         int64_t(g.wa) * g.ha < (int64_t(1) << 31) && opix < (int64_t(1) << 31) &&
-         ((batched && n_alpha <= kGatherPlanes && opix * n_alpha < kGatherOut) ||
-          opix * n_alpha <= kGatherWork / (int64_t(g.wb) * g.hb));
-}
-
 hipError_t refocus_gather(const float* gamma, const RefGeom& g, const int32_t* itab,
                           const float* ftab, int64_t stride, int n_alpha, float* out,
                           hipStream_t s) {
-  if (!refocus_gather_fits(g, n_alpha, true)) return hipErrorInvalidValue;
+  if (!refocus_gather_takes(g, n_alpha)) return hipErrorInvalidValue;
   const GeomI gi{g.wa, g.ha, g.wb, g.hb, g.out_w, g.out_h};
   const int64_t opix = int64_t(g.out_w) * g.out_h;
   hipLaunchKernelGGL(k_ref_gather, dim3(unsigned((opix + 15) / 16), unsigned(n_alpha)), dim3(256),
