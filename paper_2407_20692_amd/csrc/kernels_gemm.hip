@@ -129,9 +129,21 @@ __device__ __forceinline__ void store_out(T v, T* p, bool past) {
     *p = v;
 }
 
+// The sum of a row or column of outputs: S and, in EPI_STREAM64, the chunk's.
+struct SideSum {
+  int64_t s, c;
+};
+template <int MODE>
+__device__ __forceinline__ SideSum side_sum(const int64_t* sum, const int64_t* csum, int64_t i) {
+  SideSum v{0, 0};
+  if constexpr (MODE != EPI_STORE64 && MODE != EPI_ADD64) v.s = sum[i];
+  if constexpr (MODE == EPI_STREAM64) v.c = csum[i];
+  return v;
+}
 template <int MODE, bool VM>
 __device__ __forceinline__ void store_result(const Epi& g, double y, bool past, int64_t q,
-                                             int64_t p, int64_t s, int64_t o) {
+                                             int64_t p, int64_t s, int64_t o, SideSum a,
+                                             SideSum b) {
   // s: sum of products in the operand domain; o: operand offset (0 or 128)
   const int64_t idx_vm = q * g.pa + p;
   const int64_t n = g.n;
@@ -154,7 +166,7 @@ __device__ __forceinline__ void store_result(const Epi& g, double y, bool past, 
     }
     case EPI_STREAM64: {
       // back to raw values: sum (a-o)(b-o) = S_ab - o S_a - o S_b + k o^2
-      const int64_t raw = s + o * (g.csum_a[p] + g.csum_b[q]) - g.kchunk * o * o;
+      const int64_t raw = s + o * (a.c + b.c) - g.kchunk * o * o;
       const int64_t t = g.acc64[idx_vm] + raw;
       g.acc64[idx_vm] = t;
       s = t;
@@ -164,8 +176,8 @@ __device__ __forceinline__ void store_result(const Epi& g, double y, bool past, 
     default:
       break;
   }
-  const int64_t sa = g.sum_a[p] - o * n;
-  const int64_t sb = g.sum_b[q] - o * n;
+  const int64_t sa = a.s - o * n;
+  const int64_t sb = b.s - o * n;
   const int64_t numer = n * s - sa * sb;
   const double gam = quotient(double(numer), double(n) * double(n), y);
   const int64_t idx = VM ? idx_vm : p * g.pb + q;
@@ -266,16 +278,40 @@ __device__ __forceinline__ int tile_pitch(const Epi& g, int cols) {
 // output elements: along the pixels in view-major order, four at a time where
 // they are aligned, along the views in pixel-major order.  (Four elements of
 // one view per lane, stored one by one, wrote 7575 x 1353 pixel-major
-// numerators from 12345 frames in 265 us; this takes 82 us.)
+// numerators from 12345 frames in 265 us; this takes 82 us.)  Elements stored one
+// by one take the sums of their row and column from LDS behind the tile, where
+// stage_sums put them before the barrier that the tile is read behind: read from
+// memory for each element, they made a small call wait 32 times (Da 644, Db 32
+// pixels, 199 packed frames, pixel-major: 33.3 -> 28.7 us), and kept for several
+// elements at a time in registers, they cost the bit kernels their third wave.
+template <bool QUADS>
+__device__ __forceinline__ bool in_quads(const Epi& g) {
+  return QUADS && g.layout == CPI_GAMMA_VIEW_MAJOR && (g.pa & 3) == 0;
+}
+constexpr int sums_bytes(int rows, int cols) { return (rows + cols) * int(sizeof(SideSum)); }
+template <int MODE, bool QUADS, int ROWS, int COLS>
+__device__ __forceinline__ void stage_sums(const Epi& g, SideSum* sums, int64_t q0, int64_t p0) {
+  if (in_quads<QUADS>(g)) return;
+  for (int t = threadIdx.x; t < COLS + ROWS; t += blockDim.x) {
+    SideSum v{0, 0};
+    if (t < COLS) {
+      if (p0 + t < g.pa) v = side_sum<MODE>(g.sum_a, g.csum_a, p0 + t);
+    } else if (q0 + t - COLS < g.pb) {
+      v = side_sum<MODE>(g.sum_b, g.csum_b, q0 + t - COLS);
+    }
+    sums[t] = v;   // columns, then rows
+  }
+}
 template <int MODE, bool QUADS, int ROWS, int COLS, int T>
-__device__ __forceinline__ void store_tile(const Epi& g, const int32_t* tile, int pitch,
-                                           int64_t q0, int64_t p0, int64_t o, int32_t pad) {
+__device__ __forceinline__ void store_tile(const Epi& g, const int32_t* tile,
+                                           const SideSum* sums, int pitch, int64_t q0,
+                                           int64_t p0, int64_t o, int32_t pad) {
   static_assert(T % (COLS / 4) == 0 && COLS % 4 == 0, "tile shape");
   const int t = threadIdx.x;
   const double y = 1.0 / (double(g.n) * double(g.n));
   const bool vm = g.layout == CPI_GAMMA_VIEW_MAJOR;
   if constexpr (QUADS) {
-    if (vm && (g.pa & 3) == 0) {
+    if (in_quads<QUADS>(g)) {
       const int cq = 4 * (t % (COLS / 4));
       const int64_t p = p0 + cq;
       if (p >= g.pa) return;
@@ -288,28 +324,31 @@ __device__ __forceinline__ void store_tile(const Epi& g, const int32_t* tile, in
       return;
     }
   }
-  // (past the caches where the 64 elements of 4 bytes that a wave stores at
-  // a time are whole 128-byte lines)
+  // Element by element: a thread keeps its column (view-major) or row; past the
+  // caches where the 64 elements of 4 bytes that a wave stores at a time are whole
+  // 128-byte lines.
+  static_assert(T % COLS == 0 && T % ROWS == 0, "tile shape");
   const int32_t rows = int32_t(g.pb - q0 < ROWS ? g.pb - q0 : ROWS);
   const int32_t cols = int32_t(g.pa - p0 < COLS ? g.pa - p0 : COLS);
-  if (vm) {
-    const bool past = (g.pa & 31) == 0;
-#pragma unroll 2
-    for (int i = t; i < ROWS * COLS; i += T) {
-      const int row = i / COLS, col = i % COLS;
-      if (row < rows && col < cols)
-        store_result<MODE, true>(g, y, past, q0 + row, p0 + col, tile[row * pitch + col] - pad, o);
+  auto run = [&](auto view_major, int fixed, int fixed_n, int first, int step, int n) {
+    constexpr bool VM = decltype(view_major)::value;
+    if (fixed >= fixed_n) return;
+    const bool past = ((VM ? g.pa : g.pb) & 31) == 0;
+    const SideSum own = sums[VM ? fixed : COLS + fixed];
+    // (two elements with their states would cost the bit kernels their third wave)
+    constexpr int kUnroll = MODE == EPI_STREAM32 || MODE == EPI_STREAM64 ? 1 : 2;
+#pragma unroll kUnroll
+    for (int k = first; k < n; k += step) {
+      const int row = VM ? k : fixed, col = VM ? fixed : k;
+      const SideSum other = sums[VM ? COLS + k : k];
+      store_result<MODE, VM>(g, y, past, q0 + row, p0 + col, tile[row * pitch + col] - pad, o,
+                             VM ? own : other, VM ? other : own);
     }
-  } else {
-    const bool past = (g.pb & 31) == 0;
-#pragma unroll 2
-    for (int i = t; i < ROWS * COLS; i += T) {
-      const int row = i % ROWS, col = i / ROWS;
-      if (row < rows && col < cols)
-        store_result<MODE, false>(g, y, past, q0 + row, p0 + col, tile[row * pitch + col] - pad,
-                                  o);
-    }
-  }
+  };
+  if (vm)
+    run(std::true_type{}, t % COLS, cols, t / COLS, T / COLS, rows);
+  else
+    run(std::false_type{}, t % ROWS, rows, t / ROWS, T / ROWS, cols);
 }
 
 // Register-fed contraction of bit rows (for comparison: CPI_GEMM_FEED=regs).
@@ -414,10 +453,12 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
         const int64_t q = m0 + 16 * i + 4 * kg + t;
         const int64_t p = n0 + 16 * j + r;
         if (q >= e.pb || p >= e.pa) continue;
+        const SideSum a = side_sum<MODE>(e.sum_a, e.csum_a, p);
+        const SideSum b = side_sum<MODE>(e.sum_b, e.csum_b, q);
         if (e.layout == CPI_GAMMA_VIEW_MAJOR)
-          store_result<MODE, true>(e, y, true, q, p, int64_t(acc[i][j][t]), 0);
+          store_result<MODE, true>(e, y, true, q, p, int64_t(acc[i][j][t]), 0, a, b);
         else
-          store_result<MODE, false>(e, y, true, q, p, int64_t(acc[i][j][t]), 0);
+          store_result<MODE, false>(e, y, true, q, p, int64_t(acc[i][j][t]), 0, a, b);
       }
 }
 
@@ -596,8 +637,9 @@ __device__ __forceinline__ void gemm_lds(const GemmArgs& g, uint8_t* stage) {
   // Epilogue through LDS, one half of the tile (64 rows) at a time: the two
   // waves owning those rows store their sums (exact integers) into a padded
   // row-major tile, which the whole work-group then writes out.
-  static_assert(64 * 132 * 4 <= S * kStage, "epilogue tile fits the stages");
+  static_assert(64 * 132 * 4 + sums_bytes(64, 128) <= S * kStage, "epilogue tile fits the stages");
   int32_t* tile = reinterpret_cast<int32_t*>(stage);
+  SideSum* sums = reinterpret_cast<SideSum*>(stage + 64 * 132 * 4);
   const Epi e{g.mode,   g.layout, g.pa,        g.pb,    g.n,     g.kchunk, g.sum_a, g.sum_b,
               g.csum_a, g.csum_b, g.gamma,     g.gamma_f32, g.numer, g.acc64,  g.acc32};
   const int pitch = tile_pitch(e, 128);
@@ -612,8 +654,9 @@ __device__ __forceinline__ void gemm_lds(const GemmArgs& g, uint8_t* stage) {
           for (int u = 0; u < 4; ++u)
             tile[(16 * i + 4 * kg + u) * pitch + wn * 64 + 16 * j + r] = int32_t(acc[i][j][u]);
     }
+    stage_sums<MODE, true, 64, 128>(e, sums, mb + 64 * h, nb);
     __syncthreads();
-    store_tile<MODE, true, 64, 128, 256>(e, tile, pitch, mb + 64 * h, nb, 0, 0);
+    store_tile<MODE, true, 64, 128, 256>(e, tile, sums, pitch, mb + 64 * h, nb, 0, 0);
     __syncthreads();
   }
 }
@@ -764,9 +807,12 @@ __device__ __forceinline__ void bytes_epilogue(const GemmArgs& g, uint8_t* stage
   constexpr int FP = FM < 4 ? FM : 4;            // fragment rows per pass
   constexpr int ROWS = FM < 4 ? TM : 16 * FP;    // rows staged per pass
   constexpr int PASSES = TM / ROWS;
-  static_assert(ROWS * (TN + 4) * 4 <= BYTES, "epilogue tile fits the stages");
+  static_assert(ROWS * (TN + 4) * 4 + sums_bytes(ROWS, TN) <= BYTES,
+                "epilogue tile fits the stages");
+  constexpr bool quads = MODE == EPI_FINAL || MODE == EPI_STREAM64;
   static_assert(PASSES == 1 || PASSES == WM * FM / FP, "epilogue passes");
   int32_t* tile = reinterpret_cast<int32_t*>(stage);
+  SideSum* sums = reinterpret_cast<SideSum*>(stage + ROWS * (TN + 4) * 4);
   const Epi e{g.mode,   g.layout, g.pa,        g.pb,    g.n,     g.kchunk, g.sum_a, g.sum_b,
               g.csum_a, g.csum_b, g.gamma,     g.gamma_f32, g.numer, g.acc64,  g.acc32};
   const int64_t o = offset ? 128 : 0;
@@ -784,9 +830,9 @@ __device__ __forceinline__ void bytes_epilogue(const GemmArgs& g, uint8_t* stage
             tile[((PASSES == 1 ? wm * 16 * FM : 0) + 16 * i + 4 * kg + u) * pitch +
                  wn * 16 * FN + 16 * j + r] = acc[h % (FM / FP) * FP + i][j][u];
     }
+    stage_sums<MODE, quads, ROWS, TN>(e, sums, mb + ROWS * h, nb);
     __syncthreads();
-    constexpr bool quads = MODE == EPI_FINAL || MODE == EPI_STREAM64;
-    store_tile<MODE, quads, ROWS, TN, T>(e, tile, pitch, mb + ROWS * h, nb, o, pad);
+    store_tile<MODE, quads, ROWS, TN, T>(e, tile, sums, pitch, mb + ROWS * h, nb, o, pad);
     __syncthreads();
   }
 }
