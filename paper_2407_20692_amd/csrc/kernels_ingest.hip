@@ -638,16 +638,16 @@ hipError_t ingest_bits(const IngestJob& a, const IngestJob& b, int64_t n, int64_
   if (kpad_bits % kBitsTileFr != 0 || n > kpad_bits || kpad_bits / 32 >= (int64_t(1) << 19))
     return hipErrorInvalidValue;
   const bool aligned = (((a.npix + 7) / 8) & 3) == 0 && (((b.npix + 7) / 8) & 3) == 0;
-  // tiles for the tile kernel: with rows of whole words, and with others from 6
-  // MiB of frames on, below which the tail kernel's short threads, in one
-  // launch, are as fast.  Whole calls, tail kernel alone / with tiles, us, Da and
-  // Db of 7575 and 1353 pixels: 4200 frames (4.7 MB) 82 / 88, 12345 (13.8 MB)
-  // 149 / 120, 50000 485 / 294; 40007 and 2001 pixels: 1100 frames (5.8 MB)
-  // 213 / 220, 2100 (11 MB) 250 / 241, 12345 695 / 502; 4225 and 1089 pixels:
-  // 12345 frames (8.2 MB) 110 / 101.
+  // tiles for the tile kernel: with rows of whole words, and with others from 8
+  // MiB of frames on: up to there the tail kernel's one launch has at most one
+  // work-group per CU.  Whole calls, tail kernel alone / with tiles, us, Da and Db
+  // of 7575 and 1353 pixels: 8.0 MB 93 / 107, 8.5 MB 113 / 107, 24 MB 213 / 163;
+  // 40007 and 2001 pixels: 257 / 270, 280 / 270, 393 / 370; 10500 and 3560:
+  // 150 / 163, 173 / 163, 317 / 267; 1001 and 999: 103 / 107, 123 / 110, 273 / 220;
+  // 300 and 300 (whose rows are half padding): 6.0 MB 170 / 177, 6.5 MB 200 / 183.
   const int64_t row_bytes = (a.npix + 7) / 8 + (b.npix + 7) / 8;
   const bool any = (a.npix + 7) / 8 >= 4 && (b.npix + 7) / 8 >= 4 &&
-                   n >= (int64_t(6) << 20) / row_bytes;
+                   n >= (int64_t(8) << 20) / row_bytes;
   const int64_t full = aligned || any ? n / kBitsTileFr : 0;
   const int64_t groups0 = (a.npix_pad + kBitsTilePix - 1) / kBitsTilePix;
   const int64_t groups = groups0 + (b.npix_pad + kBitsTilePix - 1) / kBitsTilePix;
