@@ -464,11 +464,16 @@ __global__ void k_select_i64(int64_t* __restrict__ dst, const int64_t* __restric
 // consecutive pixels (one dword, 4 pixels, per lane and frame) and a slice of
 // 64-frame units: 4 x 4 byte transposes in registers turn a unit's 64 dwords
 // into one 64-byte row segment per pixel, which the lane writes with four
-// consecutive 16-byte stores.  Pads (frames >= n, pixels >= npix of aligned
-// rows) are written as 0.  Bound by HBM: every byte read and written once
+// consecutive 16-byte stores.  Pads (frames >= n, pixels >= npix) are written as 0.
+// WORDS: frame rows are a multiple of 4 bytes long; else, with rows of at least 4
+// bytes (ANY), words are loaded from any byte, and a row's last one as the row's
+// last four bytes, shifted; else byte by byte.  (Byte by byte for any row length
+// took 14.7 us where this takes 8.1: Da 30, Db 32 pixels, 68 frames.)
+// Bound by HBM: every byte read and written once
 // (Da 128 x 128, Db 64 x 64, 20000 frames: 410 + 410 MB in 230 us; the byte-wise
 // transpose through LDS that it replaces took 802 us, and a sums pass 101).
-template <bool ALIGNED>
+enum ByteLoad : int { WORDS, ANY, BYTES };
+template <int LOAD>
 __global__ __launch_bounds__(256) void k_u8_to_bytes(IngestJob j0, IngestJob j1, int64_t groups0,
                                                      int64_t n, int64_t pitch, int64_t nunits,
                                                      int64_t units_per_slice,
@@ -492,19 +497,24 @@ __global__ __launch_bounds__(256) void k_u8_to_bytes(IngestJob j0, IngestJob j1,
   int64_t u1 = u0 + units_per_slice;
   if (u1 > nunits) u1 = nunits;
   const bool pin = px < npix;
-  const uint32_t lane_off = uint32_t(pin ? px : 0);
+  const bool part = LOAD == ANY && pin && px + 4 > npix;
+  const uint32_t lane_off = uint32_t(part ? npix - 4 : pin ? px : 0);
   const uint32_t pmask = pin ? 0xffffffffu : 0u;
+  const int shift = part ? 8 * int(px + 4 - npix) : 0;
   auto load = [&](int64_t f) -> uint32_t {
     const uint8_t* row = frames + f * npix;
-    if constexpr (ALIGNED) {
+    if constexpr (LOAD == WORDS) {
       return *reinterpret_cast<const uint32_t*>(row + lane_off);
+    } else if constexpr (LOAD == ANY) {
+      struct __attribute__((packed)) AnyWord {
+        uint32_t v;
+      };
+      return reinterpret_cast<const AnyWord*>(row + lane_off)->v >> shift;
     } else {
       uint32_t v = 0;
 #pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const uint32_t o = px + b < npix ? uint32_t(px + b) : 0u;
-        v |= uint32_t(row[o]) << (8 * b);
-      }
+      for (int b = 0; b < 4; ++b)
+        v |= (px + b < npix ? uint32_t(row[px + b]) : 0u) << (8 * b);
       return v;
     }
   };
@@ -721,7 +731,9 @@ hipError_t u8_to_bytes(const IngestJob& a, const IngestJob& b, int64_t n, int64_
   const int64_t ups = (nunits + slices - 1) / slices;
   const int64_t used = (nunits + ups - 1) / ups;
   if (groups > 0x7fffffff) return hipErrorInvalidValue;
-  auto* kern = ((a.npix | b.npix) & 3) == 0 ? k_u8_to_bytes<true> : k_u8_to_bytes<false>;
+  auto* kern = ((a.npix | b.npix) & 3) == 0     ? k_u8_to_bytes<WORDS>
+               : a.npix >= 4 && b.npix >= 4 ? k_u8_to_bytes<ANY>
+                                            : k_u8_to_bytes<BYTES>;
   hipLaunchKernelGGL(kern, dim3(unsigned(groups), unsigned(used)), dim3(256), 0, s, a, b, groups0,
                      n, row_bytes, nunits, ups, stats);
   return hipGetLastError();
