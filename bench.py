@@ -748,7 +748,7 @@ def pmc_summary(kind, key):
     if key is None:
         return None
     name = {"gemm": f"gemm_f4lds_{key[0]}_pmc.txt", "refocus": f"ref_sep_{key[1]}_pmc.txt",
-            "refocus_rows": f"ref_rows_{key[1]}_pmc.txt"}[kind]
+            "refocus_rows": f"ref_window_{key[1]}_pmc.txt"}[kind]
     return os.path.join(ROOT, "profiles", name)
 
 

@@ -935,9 +935,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_gemm_bytes(GemmArgs g) {
   gemm_bytes<MODE, FM, FN, WM, WN, S>(g, stage);
 }
 
-// The 256 x 256 tile.  Copies take 128 bytes (two K steps) of a row at a time:
-// L2 serves whole aligned 128-byte lines at 20 to 23 TB/s here, 64-byte pieces
-// at 10 to 12 (a register-free copy loop over 16 MB), and the tile needs 11.
+// The 256 x 256 tile.  Copies take 128 bytes (two K steps) of a row at a time, whole
+// lines, which L2 serves faster than 64-byte pieces (times below).
 // Rows of a workspace of the reported size start at multiples of 128 bytes.
 // Stage: 8 rows x 128 bytes per copy instruction, chunk c (16 bytes) of row r
 // at slot 8 (r % 8) + (c ^ swz(r)), swz chosen as lds_swizzle is, for 128-byte
@@ -947,7 +946,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_gemm_bytes(GemmArgs g) {
 // 128 bytes.
 // Measured (Da 128 x 128, Db 64 x 64, 20000 frames): 1.24 ms; with 64-byte copies
 // 1.39 ms (four or five stages alike), with 128-byte copies of rows that start
-// at odd multiples of 64 bytes 1.33 ms.  The matrix ops alone take 0.66 ms.
+// at odd multiples of 64 bytes 1.33 ms.  The matrix ops take 0.60 ms of it at the
+// rate of a register-only loop of them (4.46 POP/s).
 constexpr int kBigStage = 65536;
 
 template <int MODE>

@@ -27,7 +27,7 @@ __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float(uint3
 
 // Round to nearest even; NaN stays a (quiet) NaN.  (One instruction; over all
 // 2^32 inputs the same as (u + 0x7FFF + (u >> 16 & 1)) >> 16, and u >> 16 | 0x40
-// for NaN.)
+// for NaN: test_gpu_bf16_rounding.)
 __device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, __bf16(f)); }
 // two floats, a in the low half
 __device__ __forceinline__ uint32_t pack_bf(float a, float b) {

@@ -4,7 +4,8 @@
 //
 // What bounds it: two multiply-adds per (plane, x_r, view row, x_b) on the
 // vector ALUs (no packed FP32): 7 ms at Da 256 x 256, Db 128 x 128 and 128
-// planes if nothing else were issued and every row and column were needed.
+// planes if nothing else were issued and every row and column were needed (of
+// which the skipped ones leave 6.0).
 // The LDS-tap form (k_ref_rows) reads 16 bytes per lane, pair and view from
 // LDS instead; there the LDS sets the pace.
 //
@@ -35,14 +36,16 @@
 //
 // Measured, x pass and whole refocus: Da 256 x 256, Db 128 x 128, 128 planes
 // 18.8 -> 11.1 ms and 20.1 -> 12.4 ms; Da 128 x 128, Db 64 x 64, 32 planes 0.465 ->
-// 0.24 ms and 0.470 -> 0.29 ms; results bit-identical to k_ref_rows.  What is left
-// (large size): the multiply-adds take 6.5 ms of vector-ALU time; with two
-// waves per SIMD they overlap only in part with the scalar instructions (0.7
-// per multiply-add in all) and the hand-overs.  Without copies the pass takes
-// 10 ms.  Raising the priority of waves that multiply (the other wave of the
-// SIMD fills their gaps) gave 2%, whole-line copies of 32 columns nothing, and
-// reading the next window under the multiply-adds, into the half of the
-// registers that a narrow one leaves, nothing.
+// 0.24 ms and 0.470 -> 0.28 ms; results bit-identical to k_ref_rows.  What is left
+// (large size, by the counters): the vector ALUs are busy 57% of the time, 95% of
+// that with multiply-adds (6.0 ms); 0.59 scalar and 0.12 other instructions go
+// with each multiply-add, two waves per SIMD overlap them only in part, and the
+// waves wait for memory or a barrier in a quarter of their cycles.  No LDS bank
+// conflicts; Gamma is fetched 15 times (65 GB), T written once.  Raising the
+// priority of waves that multiply (the other wave of the SIMD fills their gaps)
+// gave 2%, whole-line copies of 32 columns nothing, and reading the next window
+// under the multiply-adds, into the half of the registers that a narrow one
+// leaves, nothing.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -55,6 +58,7 @@ namespace cpi {
 namespace {
 
 constexpr int kWinWaveWords = 176;   // table words per wave and view
+static_assert(kWinWaveWords * 4 <= 12 * kWinPairs, "plan_refocus reserves 12 bytes per pair");
 constexpr int kWinTabBytes = kWinWaves * 512;   // of which the weights are staged in LDS
 constexpr int kWinMaxGroups = 64;    // plane groups per chunk (256 planes in groups of 4 or more)
 
@@ -238,7 +242,7 @@ __global__ __launch_bounds__(256) void k_window_xtab(GeomI g, const int32_t* __r
 #define CPI_WIN_PAIR(x, y, a, b, i)                              \
   CPI_WIN_DPP(a, x, v168, i)   CPI_WIN_DPP(b, x, v208, i)        \
   CPI_WIN_DPP(a, y, v169, i) CPI_WIN_DPP(b, y, v209, i)
-// four pairs whose cells are the bytes of register c
+// two pairs whose cells are the 16-bit halves of register c
 #define CPI_WIN_TWO(c, x, y, a0, b0, i0, a1, b1, i1)                  \
   "s_mov_b32 m0, " #c "\n" CPI_WIN_PAIR(x, y, a0, b0, i0)             \
   "s_lshr_b32 m0, " #c ", 16\n" CPI_WIN_PAIR(x, y, a1, b1, i1)

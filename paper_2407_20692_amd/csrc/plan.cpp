@@ -200,9 +200,11 @@ cpi_status plan_refocus(const cpi_geometry* g, int32_t n_alpha, RefocusPlan* p,
   q.rows_chunk = chunk;
   q.partial_bytes = std::max(q.partial_bytes, size_t(chunk) * t_plane);
   off = align256(off + q.partial_bytes);
-  // per-view tables of one chunk: 3 words per (plane, output column, view
-  // column) and a 4-word header per 64 or more pairs; touched-row ranges (at
-  // most one per plane and lens-plane row)
+  // per-view tables of one chunk: with LDS taps 3 words per (plane, output
+  // column, view column) and a 4-word header per 64 or more pairs, with the window
+  // in registers 176 words per 64 pairs; pairs are padded to the chunk's multiple
+  // of 16 planes and to 64 columns at most.  Touched-row ranges (at most one per
+  // plane and lens-plane row).
   const size_t pairs = size_t(chunk) * size_t(q.rows_wout_cap) * size_t(g->wb);
   q.off_rows_xe = off;
   off = align256(off + pairs * 12 + pairs / 4 + 16);

@@ -52,7 +52,8 @@ struct CorrPlan {
 };
 
 // Fills `p`; returns CPI_OK or an error with `why` set.  byte_row_align: 128
-// (whole cache lines, which the byte contraction reads at twice the rate) or
+// (whole cache lines: the byte contraction takes 1.24 instead of 1.33 ms at 16384 x
+// 4096 pixels, 20000 frames) or
 // 64 (the smallest workspace).
 constexpr int64_t kByteRowLine = 128;
 cpi_status plan_correlate(int64_t n, int64_t pa, int64_t pb, int fmt, CorrPlan* p,
