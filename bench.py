@@ -908,7 +908,7 @@ def streaming_bench(args, cpi, torch, np, dev):
     res.update(one)
     two["mode"] = ("refocus of chunk k on a second stream while chunk k + 1 is folded (two FP32 "
                    "Gamma buffers); the two streams' kernels share the CUs, and the gain depends "
-                   "on how the runtime places the streams on its hardware queues (1.1-1.33e6 "
+                   "on how the runtime places the streams on its hardware queues (1.1-1.98e6 "
                    "frames/s measured over runs)")
     res["two_stream_refocus"] = two
     return res
